@@ -17,7 +17,7 @@
 //            128-query tile looping over key tiles.  No atomics.
 // head_dim 80 = three 32-wide MFMA K-steps, the last zero-padded in the register
 // operand; output d-tiles of 16.
-// fp32 kernels (the small fp32 configuration): plain per-row loops.
+// fp32 kernels (the small fp32 configurations): fp32 MFMA, described with them below.
 #include "common.h"
 #include "internal.h"
 
@@ -709,134 +709,347 @@ __global__ __launch_bounds__(64 * (8 / NS), NS == 2 ? 3 : 1) void attn_bwd_dq_ke
   }
 }
 
-// ---- -delta = -rowsum(dO o O) per (head, query), stored negated --------------------------
+// ---- fp32 kernels ------------------------------------------------------------------
+//
+// Per (16-row sub-tile of a work item, head) one block of four waves; the waves take the
+// segment's 16-row tiles of the other operand in turn (tile w, w + 4, ...) and their
+// partial results are added in wave order through LDS.  All products run on
+// v_mfma_f32_16x16x4_f32: in an operand fragment lane (g, r) = (l / 16, l % 16) holds row
+// (or column) r at reduction index g.  Two ways of taking a 16 x D tile as an operand:
+//   row form         lane reads 16-byte pieces of row r; piece f gives the reduction
+//                    indices d = 16f + 4g + s of four successive MFMAs s
+//   transposed form  lane reads X[4g + s][16 dt + r], one value per MFMA s: the reduction
+//                    runs over the tile's rows in the order in which a score accumulator
+//                    (row 4g + s in element s) already holds its other operand
+// so scores never leave their registers, and each operand goes from L2 to registers with
+// the next tile's loads in flight during the MFMAs (no LDS, no barrier in the loop).
+// Splitting the other operand's tiles over waves is what fills the chip: an encoder of
+// 1,040 rows and 6 heads has 54 (128-row tile, head) pairs but 390 sub-tiles.  Measured on
+// MI355X at that size (segments 256 / 432 / 352, d = 64), before (one thread per row):
+// forward 2780 us, dQ 1270 + 52 (delta), dK/dV 2064; now 20 us, 58 (with delta, beside the
+// side stream's weight gradients), 34.
+constexpr int F32_SUB = ATTN_TILE / 16;   // 16-row sub-tiles of a work item
 
-template <class T>
-__global__ void attn_delta_kernel(const T* O, const T* dO, int64_t ldo, int64_t N, int heads,
-                                  int d, float* delta) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= N * heads) return;
-  const int64_t q = i / heads;
-  const int hd = (int)(i % heads);
-  float s = 0.f;
-  for (int e = 0; e < d; ++e)
-    s += to_f(O[q * ldo + hd * d + e]) * to_f(dO[q * ldo + hd * d + e]);
-  delta[(int64_t)hd * N + q] = -s;
+// Row form of rows r0.. (clamped to `last`): piece f at X[row][16f + 4g].
+template <int D> struct RowsF32 {
+  float4 v[D / 16];
+};
+template <int D>
+__device__ __forceinline__ void load_rows(RowsF32<D>& R, const float* X, int64_t ld, int row,
+                                          int last, int g) {
+  const float* p = X + (int64_t)min(row, last) * ld + 4 * g;
+#pragma unroll
+  for (int f = 0; f < D / 16; ++f) R.v[f] = *reinterpret_cast<const float4*>(p + 16 * f);
+}
+// Transposed form of rows r0 + 4g + s; rows past `last` are zero.
+template <int D> struct ColsF32 {
+  float v[4][D / 16];
+};
+template <int D>
+__device__ __forceinline__ void load_cols(ColsF32<D>& C, const float* X, int64_t ld, int r0,
+                                          int last, int g, int r) {
+#pragma unroll
+  for (int s = 0; s < 4; ++s) {
+    const int row = r0 + 4 * g + s;
+    const float* p = X + (int64_t)min(row, last) * ld + r;
+#pragma unroll
+    for (int dt = 0; dt < D / 16; ++dt) {
+      const float x = p[16 * dt];
+      C.v[s][dt] = row <= last ? x : 0.f;
+    }
+  }
+}
+// acc[4g + s][r] += sum_d A[row 4g + s][d] B[row r][d], both in row form
+template <int D>
+__device__ __forceinline__ f32x4 dot_rows(const RowsF32<D>& A, const RowsF32<D>& B, f32x4 acc) {
+#pragma unroll
+  for (int f = 0; f < D / 16; ++f) {
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(A.v[f].x, B.v[f].x, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(A.v[f].y, B.v[f].y, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(A.v[f].z, B.v[f].z, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(A.v[f].w, B.v[f].w, acc, 0, 0, 0);
+  }
+  return acc;
+}
+// acc[dt] (element s: component 16 dt + 4g + s of row r) += sum over the tile's rows
+template <int D>
+__device__ __forceinline__ void accum_cols(f32x4 (&acc)[D / 16], const ColsF32<D>& A,
+                                           const f32x4& b) {
+#pragma unroll
+  for (int s = 0; s < 4; ++s)
+#pragma unroll
+    for (int dt = 0; dt < D / 16; ++dt)
+      acc[dt] = __builtin_amdgcn_mfma_f32_16x16x4f32(A.v[s][dt], b[s], acc[dt], 0, 0, 0);
+}
+// Sum of the four waves' accumulators in wave order, in wave 0.
+template <int N>
+__device__ __forceinline__ void add_waves(f32x4 (&acc)[N], f32x4 (*red)[64], int w, int l) {
+  if (w > 0) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) red[(w - 1) * N + i][l] = acc[i];
+  }
+  __syncthreads();
+  if (w == 0) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+#pragma unroll
+      for (int i = 0; i < N; ++i) acc[i] += red[k * N + i][l];
+  }
+}
+// One row's D gradients (element s of acc[dt]: component 16 dt + 4g + s), scaled; with
+// rotary positions the adjacent pairs are rotated back and written in the original order.
+template <int D>
+__device__ __forceinline__ void store_grad_f32(const AttnArgs& p, float* out, int row, int g,
+                                               const f32x4 (&acc)[D / 16]) {
+#pragma unroll
+  for (int dt = 0; dt < D / 16; ++dt) {
+    float x[4];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) x[s] = acc[dt][s] * p.scale;
+    if (p.rope_pos != nullptr) {
+      const int j = 8 * dt + 2 * g;
+      rope_unrotate(x[0], x[1], rope_cs(p.rope_pos, p.rope_tab, D, row, j));
+      rope_unrotate(x[2], x[3], rope_cs(p.rope_pos, p.rope_tab, D, row, j + 1));
+      *reinterpret_cast<float2*>(out + j) = make_float2(x[0], x[2]);
+      *reinterpret_cast<float2*>(out + j + D / 2) = make_float2(x[1], x[3]);
+    } else {
+      *reinterpret_cast<float4*>(out + 16 * dt + 4 * g) = make_float4(x[0], x[1], x[2], x[3]);
+    }
+  }
 }
 
-// ---- fp32 kernels: one thread per query (forward, dQ) or per key (dK, dV) -------------
-
+// S^T = K Q^T (a query per column), online softmax per wave, O^T += V^T P^T; the waves'
+// (max, sum, O) are merged at the end.
 template <int D>
-__global__ void attn_fwd_f32_kernel(AttnArgs p) {
-  const int work = blockIdx.x / p.heads, head = blockIdx.x % p.heads;
-  const int4 wk = p.work[work];
-  const int q = wk.x + threadIdx.x, s0 = wk.y, s1 = wk.z;
-  if (q >= s1) return;
+__global__ __launch_bounds__(256) void attn_fwd_f32_kernel(AttnArgs p) {
+  constexpr int ND = D / 16;
+  __shared__ f32x4 red[3 * ND][64];
+  __shared__ float2 ml[4][64];
+  const int sub = blockIdx.x % F32_SUB, wh = blockIdx.x / F32_SUB;
+  const int4 wk = p.work[wh / p.heads];
+  const int head = wh % p.heads;
+  const int q0 = wk.x + 16 * sub, s0 = wk.y, last = wk.z - 1;
+  if (q0 > last) return;
+  const int w = threadIdx.x >> 6, l = threadIdx.x & 63, g = l >> 4, r = l & 15;
   const float* Q = reinterpret_cast<const float*>(p.q) + head * D;
   const float* K = reinterpret_cast<const float*>(p.k) + head * D;
   const float* V = reinterpret_cast<const float*>(p.v) + head * D;
-  float qv[D], o[D];
-  for (int e = 0; e < D; ++e) {
-    qv[e] = Q[(int64_t)q * p.ld + e];
-    o[e] = 0.f;
+  const int nt = (last - s0) / 16 + 1;
+  RowsF32<D> q, k;
+  ColsF32<D> v;
+  load_rows<D>(q, Q, p.ld, q0 + r, last, g);
+  float m = -INFINITY, sum = 0.f;
+  f32x4 o[ND];
+#pragma unroll
+  for (int dt = 0; dt < ND; ++dt) o[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+  if (w < nt) {
+    load_rows<D>(k, K, p.ld, s0 + 16 * w + r, last, g);
+    load_cols<D>(v, V, p.ld, s0 + 16 * w, last, g, r);
   }
-  float m = -INFINITY, lsum = 0.f;
-  for (int k = s0; k < s1; ++k) {
-    float s = 0.f;
-    for (int e = 0; e < D; ++e) s += qv[e] * K[(int64_t)k * p.ld + e];
-    s *= p.scale;
-    const float mn = fmaxf(m, s);
-    const float a = expf(m - mn), e1 = expf(s - mn);
-    lsum = lsum * a + e1;
-    for (int e = 0; e < D; ++e) o[e] = o[e] * a + e1 * V[(int64_t)k * p.ld + e];
+  for (int t = w; t < nt; t += 4) {
+    const int k0 = s0 + 16 * t;
+    RowsF32<D> kn = k;
+    ColsF32<D> vn = v;
+    if (t + 4 < nt) {
+      load_rows<D>(kn, K, p.ld, k0 + 64 + r, last, g);
+      load_cols<D>(vn, V, p.ld, k0 + 64, last, g, r);
+    }
+    f32x4 s = dot_rows<D>(k, q, f32x4{0.f, 0.f, 0.f, 0.f});
+#pragma unroll
+    for (int e = 0; e < 4; ++e) s[e] = k0 + 4 * g + e <= last ? s[e] * p.scale : -INFINITY;
+    float mx = fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3]));
+    mx = fmaxf(mx, __shfl_xor(mx, 16));
+    mx = fmaxf(mx, __shfl_xor(mx, 32));
+    const float mn = fmaxf(m, mx), a = expf(m - mn);
     m = mn;
+    sum *= a;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      s[e] = expf(s[e] - mn);
+      sum += s[e];   // this lane's keys; the lane groups are added after the loop
+    }
+#pragma unroll
+    for (int dt = 0; dt < ND; ++dt) o[dt] *= a;
+    accum_cols<D>(o, v, s);
+    k = kn;
+    v = vn;
   }
-  float* Ot = reinterpret_cast<float*>(p.out) + head * D;
-  for (int e = 0; e < D; ++e) Ot[(int64_t)q * p.ldo + e] = o[e] / lsum;
-  if (p.lse) p.lse[(int64_t)head * p.N + q] = m + logf(lsum);
+  sum += __shfl_xor(sum, 16);
+  sum += __shfl_xor(sum, 32);
+  ml[w][l] = make_float2(m, sum);
+  __syncthreads();
+  // wave 0 always has a tile, so the common maximum is a real score's; a wave without
+  // tiles has weight 0
+  float M = ml[0][l].x, tot = 0.f;
+#pragma unroll
+  for (int i = 1; i < 4; ++i) M = fmaxf(M, ml[i][l].x);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) tot += ml[i][l].y * expf(ml[i][l].x - M);
+  const float mine = expf(m - M);
+#pragma unroll
+  for (int dt = 0; dt < ND; ++dt) o[dt] *= mine;
+  add_waves<ND>(o, red, w, l);
+  const int row = q0 + r;
+  if (w > 0 || row > last) return;
+  float* O = reinterpret_cast<float*>(p.out) + head * D + (int64_t)row * p.ldo;
+#pragma unroll
+  for (int dt = 0; dt < ND; ++dt)
+    *reinterpret_cast<float4*>(O + 16 * dt + 4 * g) =
+        make_float4(o[dt][0] / tot, o[dt][1] / tot, o[dt][2] / tot, o[dt][3] / tot);
+  if (g == 0 && p.lse) p.lse[(int64_t)head * p.N + row] = M + logf(tot);
 }
 
+// dQ^T += K^T dS^T over the segment's keys; also -delta = -rowsum(dO o O) of its queries.
 template <int D>
-__global__ void attn_bwd_dq_f32_kernel(AttnArgs p) {
-  const int work = blockIdx.x / p.heads, head = blockIdx.x % p.heads;
-  const int4 wk = p.work[work];
-  const int q = wk.x + threadIdx.x, s0 = wk.y, s1 = wk.z;
-  if (q >= s1) return;
+__global__ __launch_bounds__(256) void attn_bwd_dq_f32_kernel(AttnArgs p) {
+  constexpr int ND = D / 16;
+  __shared__ f32x4 red[3 * ND][64];
+  const int sub = blockIdx.x % F32_SUB, wh = blockIdx.x / F32_SUB;
+  const int4 wk = p.work[wh / p.heads];
+  const int head = wh % p.heads;
+  const int q0 = wk.x + 16 * sub, s0 = wk.y, last = wk.z - 1;
+  if (q0 > last) return;
+  const int w = threadIdx.x >> 6, l = threadIdx.x & 63, g = l >> 4, r = l & 15;
   const float* Q = reinterpret_cast<const float*>(p.q) + head * D;
   const float* K = reinterpret_cast<const float*>(p.k) + head * D;
   const float* V = reinterpret_cast<const float*>(p.v) + head * D;
-  const float* dO = reinterpret_cast<const float*>(p.d_o) + head * D;
-  float qv[D], dov[D], dq[D];
-  for (int e = 0; e < D; ++e) {
-    qv[e] = Q[(int64_t)q * p.ld + e];
-    dov[e] = dO[(int64_t)q * p.ldo + e];
-    dq[e] = 0.f;
+  const int nt = (last - s0) / 16 + 1;
+  const int row = q0 + r, rc = min(row, last);
+  RowsF32<D> q, d_o, k, v;
+  ColsF32<D> kt;
+  load_rows<D>(q, Q, p.ld, row, last, g);
+  load_rows<D>(d_o, reinterpret_cast<const float*>(p.d_o) + head * D, p.ldo, row, last, g);
+  float del = 0.f;
+  {
+    RowsF32<D> o;
+    load_rows<D>(o, reinterpret_cast<const float*>(p.o) + head * D, p.ldo, row, last, g);
+#pragma unroll
+    for (int f = 0; f < ND; ++f)
+      del += o.v[f].x * d_o.v[f].x + o.v[f].y * d_o.v[f].y + o.v[f].z * d_o.v[f].z +
+             o.v[f].w * d_o.v[f].w;
+    del += __shfl_xor(del, 16);
+    del += __shfl_xor(del, 32);
   }
-  const float L = p.lse[(int64_t)head * p.N + q], mdel = p.delta_out[(int64_t)head * p.N + q];
-  for (int k = s0; k < s1; ++k) {
-    float s = 0.f, dp = 0.f;
-    for (int e = 0; e < D; ++e) {
-      s += qv[e] * K[(int64_t)k * p.ld + e];
-      dp += dov[e] * V[(int64_t)k * p.ld + e];
+  const float lse = p.lse[(int64_t)head * p.N + rc];
+  if (w == 0 && g == 0 && row <= last) p.delta_out[(int64_t)head * p.N + row] = -del;
+  f32x4 dq[ND];
+#pragma unroll
+  for (int dt = 0; dt < ND; ++dt) dq[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+  if (w < nt) {
+    const int k0 = s0 + 16 * w;
+    load_rows<D>(k, K, p.ld, k0 + r, last, g);
+    load_rows<D>(v, V, p.ld, k0 + r, last, g);
+    load_cols<D>(kt, K, p.ld, k0, last, g, r);
+  }
+  for (int t = w; t < nt; t += 4) {
+    const int k0 = s0 + 16 * t;
+    RowsF32<D> kn = k, vn = v;
+    ColsF32<D> ktn = kt;
+    if (t + 4 < nt) {
+      load_rows<D>(kn, K, p.ld, k0 + 64 + r, last, g);
+      load_rows<D>(vn, V, p.ld, k0 + 64 + r, last, g);
+      load_cols<D>(ktn, K, p.ld, k0 + 64, last, g, r);
     }
-    const float ds = expf(s * p.scale - L) * (dp + mdel);
-    for (int e = 0; e < D; ++e) dq[e] += ds * K[(int64_t)k * p.ld + e];
+    const f32x4 s = dot_rows<D>(k, q, f32x4{0.f, 0.f, 0.f, 0.f});
+    const f32x4 dp = dot_rows<D>(v, d_o, f32x4{0.f, 0.f, 0.f, 0.f});
+    f32x4 ds;
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      ds[e] = k0 + 4 * g + e <= last ? expf(s[e] * p.scale - lse) * (dp[e] - del) : 0.f;
+    accum_cols<D>(dq, kt, ds);
+    k = kn;
+    v = vn;
+    kt = ktn;
   }
-  float* dQ = reinterpret_cast<float*>(p.dq) + head * D + (int64_t)q * p.ldd;
-  if (p.rope_pos != nullptr) {   // pair-interleaved q, k: rotate back, original order
-    for (int j = 0; j < D / 2; ++j) {
-      float a = dq[2 * j] * p.scale, b = dq[2 * j + 1] * p.scale;
-      rope_unrotate(a, b, rope_cs(p.rope_pos, p.rope_tab, D, q, j));
-      dQ[j] = a;
-      dQ[j + D / 2] = b;
-    }
-  } else {
-    for (int e = 0; e < D; ++e) dQ[e] = dq[e] * p.scale;
-  }
+  add_waves<ND>(dq, red, w, l);
+  if (w > 0 || row > last) return;
+  store_grad_f32<D>(p, reinterpret_cast<float*>(p.dq) + head * D + (int64_t)row * p.ldd, row, g,
+                    dq);
 }
 
+// Per 16 keys: S = Q K^T (a key per column), dV^T += dO^T P, dK^T += Q^T dS over the
+// segment's queries.
 template <int D>
-__global__ void attn_bwd_dkdv_f32_kernel(AttnArgs p) {
-  const int work = blockIdx.x / p.heads, head = blockIdx.x % p.heads;
-  const int4 wk = p.work[work];
-  const int k = wk.x + threadIdx.x, s0 = wk.y, s1 = wk.z;
-  if (k >= s1) return;
+__global__ __launch_bounds__(256) void attn_bwd_dkdv_f32_kernel(AttnArgs p) {
+  constexpr int ND = D / 16;
+  __shared__ f32x4 red[3 * ND][64];
+  const int sub = blockIdx.x % F32_SUB, wh = blockIdx.x / F32_SUB;
+  const int4 wk = p.work[wh / p.heads];
+  const int head = wh % p.heads;
+  const int key0 = wk.x + 16 * sub, s0 = wk.y, last = wk.z - 1;
+  if (key0 > last) return;
+  const int w = threadIdx.x >> 6, l = threadIdx.x & 63, g = l >> 4, r = l & 15;
   const float* Q = reinterpret_cast<const float*>(p.q) + head * D;
-  const float* K = reinterpret_cast<const float*>(p.k) + head * D;
-  const float* V = reinterpret_cast<const float*>(p.v) + head * D;
   const float* dO = reinterpret_cast<const float*>(p.d_o) + head * D;
-  float kv[D], vv[D], dk[D], dv[D];
-  for (int e = 0; e < D; ++e) {
-    kv[e] = K[(int64_t)k * p.ld + e];
-    vv[e] = V[(int64_t)k * p.ld + e];
-    dk[e] = dv[e] = 0.f;
-  }
-  for (int q = s0; q < s1; ++q) {
-    float s = 0.f, dp = 0.f;
-    for (int e = 0; e < D; ++e) {
-      s += Q[(int64_t)q * p.ld + e] * kv[e];
-      dp += dO[(int64_t)q * p.ldo + e] * vv[e];
+  const float* LSE = p.lse + (int64_t)head * p.N;
+  const float* DEL = p.delta + (int64_t)head * p.N;
+  const int nt = (last - s0) / 16 + 1;
+  const int row = key0 + r;
+  RowsF32<D> k, v, q, d_o;
+  ColsF32<D> qt, dt_;
+  load_rows<D>(k, reinterpret_cast<const float*>(p.k) + head * D, p.ld, row, last, g);
+  load_rows<D>(v, reinterpret_cast<const float*>(p.v) + head * D, p.ld, row, last, g);
+  f32x4 dk[ND], dv[ND], lse, del;
+#pragma unroll
+  for (int dt = 0; dt < ND; ++dt) dk[dt] = dv[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+  auto load_stats = [&](int r0, f32x4& a, f32x4& b) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int qr = min(r0 + 4 * g + e, last);
+      a[e] = LSE[qr];
+      b[e] = DEL[qr];   // -delta as stored
     }
-    const float pp = expf(s * p.scale - p.lse[(int64_t)head * p.N + q]);
-    const float ds = pp * (dp + p.delta[(int64_t)head * p.N + q]);
-    for (int e = 0; e < D; ++e) {
-      dv[e] += pp * dO[(int64_t)q * p.ldo + e];
-      dk[e] += ds * Q[(int64_t)q * p.ld + e];
-    }
+  };
+  if (w < nt) {
+    const int r0 = s0 + 16 * w;
+    load_rows<D>(q, Q, p.ld, r0 + r, last, g);
+    load_rows<D>(d_o, dO, p.ldo, r0 + r, last, g);
+    load_cols<D>(qt, Q, p.ld, r0, last, g, r);
+    load_cols<D>(dt_, dO, p.ldo, r0, last, g, r);
+    load_stats(r0, lse, del);
   }
-  float* dK = reinterpret_cast<float*>(p.dk) + head * D + (int64_t)k * p.ldd;
-  float* dV = reinterpret_cast<float*>(p.dv) + head * D + (int64_t)k * p.ldd;
-  for (int e = 0; e < D; ++e) dV[e] = dv[e];
-  if (p.rope_pos != nullptr) {   // pair-interleaved q, k: rotate back, original order
-    for (int j = 0; j < D / 2; ++j) {
-      float a = dk[2 * j] * p.scale, b = dk[2 * j + 1] * p.scale;
-      rope_unrotate(a, b, rope_cs(p.rope_pos, p.rope_tab, D, k, j));
-      dK[j] = a;
-      dK[j + D / 2] = b;
+  for (int t = w; t < nt; t += 4) {
+    const int r0 = s0 + 16 * t;
+    RowsF32<D> qn = q, dn = d_o;
+    ColsF32<D> qtn = qt, dtn = dt_;
+    f32x4 lsen = lse, deln = del;
+    if (t + 4 < nt) {
+      load_rows<D>(qn, Q, p.ld, r0 + 64 + r, last, g);
+      load_rows<D>(dn, dO, p.ldo, r0 + 64 + r, last, g);
+      load_cols<D>(qtn, Q, p.ld, r0 + 64, last, g, r);
+      load_cols<D>(dtn, dO, p.ldo, r0 + 64, last, g, r);
+      load_stats(r0 + 64, lsen, deln);
     }
-  } else {
-    for (int e = 0; e < D; ++e) dK[e] = dk[e] * p.scale;
+    const f32x4 s = dot_rows<D>(q, k, f32x4{0.f, 0.f, 0.f, 0.f});
+    const f32x4 dp = dot_rows<D>(d_o, v, f32x4{0.f, 0.f, 0.f, 0.f});
+    f32x4 pr, ds;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const bool in = r0 + 4 * g + e <= last;
+      const float pe = expf(s[e] * p.scale - lse[e]);
+      pr[e] = in ? pe : 0.f;
+      ds[e] = in ? pe * (dp[e] + del[e]) : 0.f;
+    }
+    accum_cols<D>(dv, dt_, pr);
+    accum_cols<D>(dk, qt, ds);
+    q = qn;
+    d_o = dn;
+    qt = qtn;
+    dt_ = dtn;
+    lse = lsen;
+    del = deln;
   }
+  add_waves<ND>(dk, red, w, l);
+  __syncthreads();
+  add_waves<ND>(dv, red, w, l);
+  if (w > 0 || row > last) return;
+  float* dV = reinterpret_cast<float*>(p.dv) + head * D + (int64_t)row * p.ldd;
+#pragma unroll
+  for (int dt = 0; dt < ND; ++dt)
+    *reinterpret_cast<float4*>(dV + 16 * dt + 4 * g) =
+        make_float4(dv[dt][0], dv[dt][1], dv[dt][2], dv[dt][3]);
+  store_grad_f32<D>(p, reinterpret_cast<float*>(p.dk) + head * D + (int64_t)row * p.ldd, row, g,
+                    dk);
 }
 
 template <int D>
@@ -856,20 +1069,17 @@ hipError_t dkdv_bf16(const AttnArgs& a, hipStream_t s) {
 }
 template <int D>
 hipError_t fwd_f32(const AttnArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL(attn_fwd_f32_kernel<D>, dim3(a.n_work * a.heads), dim3(ATTN_TILE), 0, s, a);
+  hipLaunchKernelGGL(attn_fwd_f32_kernel<D>, dim3(a.n_work * a.heads * F32_SUB), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 template <int D>
 hipError_t dq_f32(const AttnArgs& a, hipStream_t s) {
-  const int64_t n = a.N * a.heads;
-  hipLaunchKernelGGL(attn_delta_kernel<float>, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s,
-                     (const float*)a.o, (const float*)a.d_o, a.ldo, a.N, a.heads, D, a.delta_out);
-  hipLaunchKernelGGL(attn_bwd_dq_f32_kernel<D>, dim3(a.n_work * a.heads), dim3(ATTN_TILE), 0, s, a);
+  hipLaunchKernelGGL(attn_bwd_dq_f32_kernel<D>, dim3(a.n_work * a.heads * F32_SUB), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 template <int D>
 hipError_t dkdv_f32(const AttnArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL(attn_bwd_dkdv_f32_kernel<D>, dim3(a.n_work * a.heads), dim3(ATTN_TILE), 0, s, a);
+  hipLaunchKernelGGL(attn_bwd_dkdv_f32_kernel<D>, dim3(a.n_work * a.heads * F32_SUB), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 

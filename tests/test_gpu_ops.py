@@ -290,3 +290,32 @@ def test_attention_fwd_bwd(dtype, heads, d):
                           ("dv", slice(2 * h, 3 * h), rdv)):
         err = max_rel(got[:, sl], ref)
         assert err < (2e-2 if dtype == "bf16" else 1e-5), (name, err)
+
+
+@pytest.mark.parametrize("heads,d", [(3, 32), (2, 64), (1, 80)])
+def test_attention_f32_tile_edges(heads, d):
+    """The fp32 attention kernels work on 16-row tiles dealt to four waves: segments of one
+    row, of a row more or less than one to five tiles (waves with no tile, with one, with two)
+    and across the 128-row work item, against the oracle.  1e-5 is some fifty roundings of
+    2^-24, more than the longest chain of a 145-row segment adds up to."""
+    import paper_2607_03229_amd as mp
+    torch, dev = torch_dev()
+    lens = [1, 15, 16, 17, 47, 49, 63, 64, 65, 80, 127, 145]
+    rng = np.random.default_rng(100 + d)
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    N, h = int(cu[-1]), heads * d
+    announce(f"fp32 attention tile edges heads={heads} d={d} N={N}")
+    qkv, dO = rnd(rng, (N, 3 * h), "f32", 1.5), rnd(rng, (N, h), "f32")
+    q, k, v = qkv[:, :h], qkv[:, h:2 * h], qkv[:, 2 * h:]
+    ro, rlse = oracle.attention(q, k, v, cu, heads, d)
+    ref = oracle.attention_bwd(q, k, v, ro, dO, rlse, cu, heads, d)
+    o, lse, dqkv = nans((N, h), "f32"), nans((heads, N), "f32"), nans((N, 3 * h), "f32")
+    scratch = torch.empty(mp.op_scratch_bytes(N, heads, h, len(lens)), dtype=torch.uint8,
+                          device=dev)
+    tq = to_dev(qkv, "f32")
+    mp.op_attention_fwd(0, tq, N, heads, d, cu, o, lse, scratch)
+    mp.op_attention_bwd(0, tq, o, to_dev(dO, "f32"), lse, N, heads, d, cu, dqkv, scratch)
+    got = host(dqkv)
+    errs = [max_rel(host(o), ro), max_rel(host(lse), rlse.T)]
+    errs += [max_rel(got[:, i * h:(i + 1) * h], ref[i]) for i in range(3)]
+    assert max(errs) < 1e-5, errs
