@@ -10,7 +10,8 @@
 // Tiling (gfx950): 256 threads = 4 wave64 in a 2x2 grid, block tile 128x128,
 // K step 64 (bf16) / 32 (fp32), each wave owns a 64x64 tile of 4x4 16x16
 // accumulators.  bf16 uses v_mfma_f32_16x16x32_bf16; fp32 uses
-// v_mfma_f32_16x16x4_f32 (eight per 32-wide K step).  LDS is double-buffered
+// v_mfma_f32_16x16x4_f32 (eight per 32-wide K step; products of few tiles take the kernel
+// of gemm_f32.hip).  LDS is double-buffered
 // (64 KB); the next tile's global loads are in flight during the MFMAs.
 // Blocks are remapped so that consecutive tiles land on the same XCD and walk
 // the output in groups of 8 tile-rows (L2 reuse of A rows and B columns).
@@ -360,6 +361,21 @@ bool takes_big(int dtype, int epi, const GemmArgs& a) {
 }
 }  // namespace
 
+namespace {
+// fp32: up to half a round of 128x128 tiles (256 CUs) goes to the 32x32 kernel, which has
+// sixteen times the blocks and four waves to a tile's K; with more tiles the larger tile's
+// reuse wins.  Measured on MI355X, us, 128x128 / 32x32 (M x N x K, tiles): 1040x1536x384
+// (108) 42 / 26, 4096x384x1536 (96) 129 / 84, 2048x1152x384 (144) 43 / 35, 1536x1536x4096
+// (144) 328 / 343, 2048x1536x384 (192) 44 / 44, 2048x2048x2048 (256) 170 / 288.  The two
+// kernels add a product's K terms in different orders.
+constexpr int64_t F32_SMALL_TILES = 128;
+bool takes_f32_small(const GemmArgs& a) {
+  const int64_t tiles = (int64_t)((a.M + BM - 1) / BM) * ((a.N + BN - 1) / BN);
+  const int64_t splits = a.kps > 0 ? (a.K + a.kps - 1) / a.kps : 1;
+  return tiles * splits <= F32_SMALL_TILES;
+}
+}  // namespace
+
 bool gemm_fused_colsum(int dtype, int layout, int epi, const GemmArgs& a) {
   return layout == GEMM_NN && epi == EPI_GELU_BWD && a.kps <= 0 && takes_big(dtype, epi, a);
 }
@@ -375,6 +391,7 @@ hipError_t gemm(int dtype, int layout, int epi, const GemmArgs& a, hipStream_t s
       case GEMM_TN: return dispatch_epi<bf16, true, true>(a, epi, s);
     }
   } else {
+    if (takes_f32_small(a)) return gemm_f32_small(layout, epi, a, s);
     switch (layout) {
       case GEMM_NT: return dispatch_epi<float, false, false>(a, epi, s);
       case GEMM_NN: return dispatch_epi<float, false, true>(a, epi, s);

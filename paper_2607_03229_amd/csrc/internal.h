@@ -54,6 +54,10 @@ hipError_t partials_reduce(float* part, float* out, int64_t rows, int n, hipStre
 // stages) and TN; same contract as gemm()
 hipError_t gemm_big(int layout, int epi, const GemmArgs& a, hipStream_t s);
 
+// fp32 problems of few 128x128 tiles: 32x32 tiles, K split over a block's waves; same
+// contract as gemm()
+hipError_t gemm_f32_small(int layout, int epi, const GemmArgs& a, hipStream_t s);
+
 struct AttnArgs {
   const void* q = nullptr;     // Q, K, V column blocks, row stride ld (head h at column h*d)
   const void* k = nullptr;

@@ -319,3 +319,29 @@ def test_attention_f32_tile_edges(heads, d):
     errs = [max_rel(host(o), ro), max_rel(host(lse), rlse.T)]
     errs += [max_rel(got[:, i * h:(i + 1) * h], ref[i]) for i in range(3)]
     assert max(errs) < 1e-5, errs
+
+
+@pytest.mark.parametrize("layout", [NT, NN, TN])
+def test_gemm_f32_tiles(layout):
+    """fp32 products at the edges of the 32x32 kernel (a K of less than one 16-deep step, of
+    one to five steps over the four waves, odd remainders, one row or column more or less than
+    a tile), split over K, and just past the tile count from which the 128x128 kernel runs
+    (1,430 x 1,424: 144 tiles).  2e-5: the bound of the other fp32 products here."""
+    import paper_2607_03229_amd as mp
+    torch, dev = torch_dev()
+    rng = np.random.default_rng(40 + layout)
+    for (M, N, K, kps) in [(1, 4, 4, 0), (32, 32, 16, 0), (33, 31, 20, 0), (31, 36, 60, 0),
+                           (64, 33, 64, 0), (65, 64, 68, 0), (40, 100, 260, 0),
+                           (36, 40, 200, 64), (1430, 1424, 36, 0)]:
+        if layout == TN:
+            M, K = (M + 3) // 4 * 4, K + (1 if K > 4 else 0)
+        announce(f"gemm f32 tiles layout={layout} M={M} N={N} K={K} kps={kps}")
+        A = rnd(rng, (K, M) if layout == TN else (M, K), "f32")
+        ldb = K if layout == NT else (N + 3) // 4 * 4
+        B = rnd(rng, (N if layout == NT else K, ldb), "f32")
+        ref = _ref_product(layout, A, B if layout == NT else B[:, :N])
+        splits = -(-K // kps) if kps else 1
+        C = nans((splits, M, N), "f32")
+        mp.op_gemm(0, layout, E_F32, M, N, K, to_dev(A, "f32"), A.shape[1], to_dev(B, "f32"),
+                   ldb, C, N, k_per_split=kps, split_stride=M * N)
+        assert max_rel(host(C).sum(0), ref) < 2e-5, (M, N, K)
