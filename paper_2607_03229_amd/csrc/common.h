@@ -71,6 +71,11 @@ __device__ __forceinline__ float gelu_grad_fast(float u) {
 __host__ __device__ __forceinline__ int rope_component(int s, int d) {
   return (s & 1) ? (s >> 1) + (d >> 1) : (s >> 1);
 }
+// The weight row behind output column n of a qkv product with `rope_cols` pair-interleaved
+// columns in heads of d.
+__device__ __forceinline__ int rope_weight_row(int n, int d, int rope_cols) {
+  return n < rope_cols ? n - n % d + rope_component(n % d, d) : n;
+}
 // (cos, sin) of rotary pair j (< d/2) of packed row `row`
 __device__ __forceinline__ float2 rope_cs(const int32_t* pos, const float2* tab, int d,
                                           int64_t row, int j) {

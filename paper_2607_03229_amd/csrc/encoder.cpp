@@ -325,33 +325,66 @@ mpipe_status pad_pe(Ctx& x, const void* patches) {
   return MPIPE_OK;
 }
 
-// Transposed copies of the [out][in] weights the next GEMMs multiply by, back to back in
-// the workspace: wt[i] = W_i^T ([in][out], row stride out), so that every forward GEMM
-// reads its weight operand K-major (whole 128-byte lines per DMA row).
-// qk_rows > 0: the first weight is the qkv weight, whose first qk_rows output rows (the q
-// and k blocks) are taken pair-interleaved within each head, so that its product comes
-// out in the layout the fused rotary epilogue and the attention kernels work on.
-mpipe_status weights_t(Ctx& x, int n, const void* const* W, const int64_t* out_f,
-                       const int64_t* in_f, const int64_t* ld, const void** wt,
-                       int qk_rows = 0) {
+// One forward Linear's weight [out][in] and how its product reads it: directly (layout NT on
+// `tile`, where the micro-batch is too small to pay for a transposed copy), or as a copy
+// [in][out] in the workspace (layout NN: every weight row of a K step is then a whole line).
+// perm: the qkv weight, whose q and k output rows are taken pair-interleaved within each
+// head, so that its product comes out in the layout the fused rotary epilogue and the
+// attention kernels work on.
+struct FwdWeight {
+  const void* W;
+  int64_t out, in, ld;
+  bool perm = false;
+  int tile = -1;             // gemm_direct_tile, or -1: transposed
+  const void* wt = nullptr;  // the transposed copy
+};
+
+// Chooses how each weight is read by a product of M rows and makes the copies (one launch).
+mpipe_status prepare_weights(Ctx& x, FwdWeight* fw, int n, int64_t M) {
   TJob jobs[kMaxTJobs];
+  int nj = 0;
   char* dst = x.ws + x.P.ws_wt;
   for (int i = 0; i < n; ++i) {
-    jobs[i].src = W[i];
-    jobs[i].lds = ld[i];
-    jobs[i].dst = dst;
-    jobs[i].ldd = out_f[i];
-    jobs[i].rows = (int)out_f[i];
-    jobs[i].cols = (int)in_f[i];
-    if (i == 0 && qk_rows > 0) {
-      jobs[i].perm_rows = qk_rows;
-      jobs[i].perm_d = x.c.d;
+    FwdWeight& f = fw[i];
+    f.tile = gemm_direct_tile(x.dt, M, f.out, f.in, f.W, f.ld);
+    if (f.tile >= 0) continue;
+    TJob& j = jobs[nj++];
+    j.src = f.W;
+    j.lds = f.ld;
+    j.dst = dst;
+    j.ldd = f.out;
+    j.rows = (int)f.out;
+    j.cols = (int)f.in;
+    if (f.perm) {
+      j.perm_rows = 2 * x.c.hidden;
+      j.perm_d = x.c.d;
     }
-    wt[i] = dst;
-    dst += out_f[i] * in_f[i] * x.E;
+    f.wt = dst;
+    dst += f.out * f.in * x.E;
   }
-  MP_CHECK(run(x.e, x.s, "transpose", 0, [&] { return transpose_batch(x.dt, jobs, n, x.s); }));
+  if (nj)
+    MP_CHECK(run(x.e, x.s, "transpose", 0, [&] { return transpose_batch(x.dt, jobs, nj, x.s); }));
   return MPIPE_OK;
+}
+
+// Y[M][out] (epilogue epi into C) = A[M][in] W^T; a: the epilogue's other arguments
+mpipe_status linear_fwd(Ctx& x, const FwdWeight& f, int epi, const void* A, int64_t lda, int64_t M,
+                        void* C, GemmArgs a) {
+  const bool direct = f.tile >= 0;
+  const GemmArgs g = ga(A, lda, direct ? f.W : f.wt, direct ? f.ld : f.out, M, f.out, f.in, C,
+                        f.out);
+  a.A = g.A;
+  a.lda = g.lda;
+  a.B = g.B;
+  a.ldb = g.ldb;
+  a.M = g.M;
+  a.N = g.N;
+  a.K = g.K;
+  a.C = g.C;
+  a.ldc = g.ldc;
+  a.tile = f.tile;
+  a.rope_rows = direct && f.perm;
+  return gemm_call(x, direct ? GEMM_NT : GEMM_NN, epi, a);
 }
 
 #define MP_RET(expr)                  \
@@ -379,12 +412,11 @@ mpipe_status forward(Ctx& x, const void* patches, void* merged, char* tape) {
   pe_operands(x, patches, Xp, Wpe, ldx);
   char* h0 = c.layers > 0 ? base + act(0).hin : mbase + MS.hfin;
   {
-    const void* wt[1];
-    const int64_t of[1] = {h}, inf[1] = {c.kp}, ld[1] = {ldx};
-    MP_RET(weights_t(x, 1, &Wpe, of, inf, ld, wt));
-    GemmArgs a = ga(Xp, ldx, wt[0], h, N, h, c.kp, h0, h);
+    FwdWeight pe{Wpe, h, c.kp, ldx};
+    MP_RET(prepare_weights(x, &pe, 1, N));
+    GemmArgs a;
     a.bias = x.W(P_PE_B);
-    MP_RET(gemm_call(x, GEMM_NN, EPI_RESID, a));
+    MP_RET(linear_fwd(x, pe, EPI_RESID, Xp, ldx, N, h0, a));
   }
   for (int l = 0; l < c.layers; ++l) {
     const ActSet& S = act(l);
@@ -399,14 +431,12 @@ mpipe_status forward(Ctx& x, const void* patches, void* merged, char* tape) {
     char* O = base + S.o;
     char* B = base + S.b;
     char* G = base + S.g;
-    // W^T of qkv, proj, fc1, fc2
-    const void* wt[4];
-    {
-      const void* W[4] = {x.W(blk_param(c, l, B_QKVW)), x.W(blk_param(c, l, B_PROJW)),
-                          x.W(blk_param(c, l, B_FC1W)), x.W(blk_param(c, l, B_FC2W))};
-      const int64_t of[4] = {3 * h, h, m, h}, inf[4] = {h, h, h, m};
-      MP_RET(weights_t(x, 4, W, of, inf, inf, wt, (int)(2 * h)));
-    }
+    // qkv, proj, fc1, fc2
+    FwdWeight fw[4] = {{x.W(blk_param(c, l, B_QKVW)), 3 * h, h, h, true},
+                       {x.W(blk_param(c, l, B_PROJW)), h, h, h},
+                       {x.W(blk_param(c, l, B_FC1W)), m, h, h},
+                       {x.W(blk_param(c, l, B_FC2W)), h, m, m}};
+    MP_RET(prepare_weights(x, fw, 4, N));
     MP_CHECK(run(x.e, x.s, "layernorm", 0, [&] {
       return layernorm_fwd(x.dt, hin, h, N, (int)h, x.W(blk_param(c, l, B_LN1G)),
                            x.W(blk_param(c, l, B_LN1B)), c.eps, A, h,
@@ -416,13 +446,13 @@ mpipe_status forward(Ctx& x, const void* patches, void* merged, char* tape) {
     {
       // q, k come out pair-interleaved per head with the 2D rotary position applied in
       // the epilogue; v in plain order
-      GemmArgs a = ga(A, h, wt[0], 3 * h, N, 3 * h, h, qkv, 3 * h);
+      GemmArgs a;
       a.bias = x.W(blk_param(c, l, B_QKVB));
       a.rope_pos = pos;
       a.rope_tab = reinterpret_cast<const float2*>(freq);
       a.rope_d = c.d;
       a.rope_cols = (int)(2 * h);
-      MP_RET(gemm_call(x, GEMM_NN, EPI_STORE_ROPE, a));
+      MP_RET(linear_fwd(x, fw[0], EPI_STORE_ROPE, A, h, N, qkv, a));
     }
     {
       AttnArgs a = attn_args(x, qkv, false);
@@ -433,11 +463,11 @@ mpipe_status forward(Ctx& x, const void* patches, void* merged, char* tape) {
       MP_CHECK(run(x.e, x.s, "attn_fwd", fl, [&] { return attention_fwd(x.dt, c.d, a, x.s); }));
     }
     {
-      GemmArgs a = ga(O, h, wt[1], h, N, h, h, hmid, h);
+      GemmArgs a;
       a.bias = x.W(blk_param(c, l, B_PROJB));
       a.aux = hin;
       a.ld_aux = h;
-      MP_RET(gemm_call(x, GEMM_NN, EPI_RESID, a));
+      MP_RET(linear_fwd(x, fw[1], EPI_RESID, O, h, N, hmid, a));
     }
     MP_CHECK(run(x.e, x.s, "layernorm", 0, [&] {
       return layernorm_fwd(x.dt, hmid, h, N, (int)h, x.W(blk_param(c, l, B_LN2G)),
@@ -446,29 +476,26 @@ mpipe_status forward(Ctx& x, const void* patches, void* merged, char* tape) {
                            reinterpret_cast<float*>(base + S.rstd2), x.s);
     }));
     {
-      GemmArgs a = ga(B, h, wt[2], m, N, m, h, G, m);
+      GemmArgs a;
       a.bias = x.W(blk_param(c, l, B_FC1B));
       a.C2 = tr ? base + S.u : nullptr;
       a.ldc2 = m;
-      MP_RET(gemm_call(x, GEMM_NN, EPI_GELU, a));
+      MP_RET(linear_fwd(x, fw[2], EPI_GELU, B, h, N, G, a));
     }
     {
-      GemmArgs a = ga(G, m, wt[3], h, N, h, m, hout, h);
+      GemmArgs a;
       a.bias = x.W(blk_param(c, l, B_FC2B));
       a.aux = hmid;
       a.ld_aux = h;
-      MP_RET(gemm_call(x, GEMM_NN, EPI_RESID, a));
+      MP_RET(linear_fwd(x, fw[3], EPI_RESID, G, m, N, hout, a));
     }
   }
   // 2x2 merger: LN, the four window rows side by side ([Tm][4h] view), fc1+GELU, fc2
   char* Z = mbase + MS.z;
   char* Gm = mbase + MS.gm;
-  const void* wtm[2];
-  {
-    const void* W[2] = {x.W(merger_param(c, M_FC1W)), x.W(merger_param(c, M_FC2W))};
-    const int64_t of[2] = {4 * h, H}, inf[2] = {4 * h, 4 * h};
-    MP_RET(weights_t(x, 2, W, of, inf, inf, wtm));
-  }
+  FwdWeight fm[2] = {{x.W(merger_param(c, M_FC1W)), 4 * h, 4 * h, 4 * h},
+                     {x.W(merger_param(c, M_FC2W)), H, 4 * h, 4 * h}};
+  MP_RET(prepare_weights(x, fm, 2, P.Tm));
   MP_CHECK(run(x.e, x.s, "layernorm", 0, [&] {
     return layernorm_fwd(x.dt, reinterpret_cast<float*>(mbase + MS.hfin), h, N, (int)h,
                          x.W(merger_param(c, M_LNG)), x.W(merger_param(c, M_LNB)), c.eps, Z, h,
@@ -476,16 +503,16 @@ mpipe_status forward(Ctx& x, const void* patches, void* merged, char* tape) {
                          reinterpret_cast<float*>(mbase + MS.rstdz), x.s);
   }));
   {
-    GemmArgs a = ga(Z, 4 * h, wtm[0], 4 * h, P.Tm, 4 * h, 4 * h, Gm, 4 * h);
+    GemmArgs a;
     a.bias = x.W(merger_param(c, M_FC1B));
     a.C2 = mt ? mbase + MS.um : nullptr;
     a.ldc2 = 4 * h;
-    MP_RET(gemm_call(x, GEMM_NN, EPI_GELU, a));
+    MP_RET(linear_fwd(x, fm[0], EPI_GELU, Z, 4 * h, P.Tm, Gm, a));
   }
   {
-    GemmArgs a = ga(Gm, 4 * h, wtm[1], H, P.Tm, H, 4 * h, merged, H);
+    GemmArgs a;
     a.bias = x.W(merger_param(c, M_FC2B));
-    MP_RET(gemm_call(x, GEMM_NN, EPI_STORE, a));
+    MP_RET(linear_fwd(x, fm[1], EPI_STORE, Gm, 4 * h, P.Tm, merged, a));
   }
   (void)E;
   return MPIPE_OK;

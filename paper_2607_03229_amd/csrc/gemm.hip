@@ -19,6 +19,7 @@
 
 #include "common.h"
 #include "internal.h"
+#include "plan.h"
 
 namespace mpipe {
 namespace {
@@ -35,9 +36,9 @@ struct Regs4 { uint4 v[4]; };
 
 // K-contiguous operand X[rows][ld]: tile rows r0..r0+127, k in [k0, k0+BK).
 // Thread t loads chunk (t & 7) of rows (t >> 3) + 32 i.
-template <class T>
+template <class T, class RowOf>
 __device__ __forceinline__ void load_kcontig(Regs4& R, const T* X, int64_t ld, int rows, int r0,
-                                             int k0, int kend) {
+                                             int k0, int kend, RowOf row_of) {
   constexpr int VEC = KStep<T>::VEC;
   const int t = threadIdx.x;
   const int c = t & 7;
@@ -45,7 +46,7 @@ __device__ __forceinline__ void load_kcontig(Regs4& R, const T* X, int64_t ld, i
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     int row = r0 + (t >> 3) + 32 * i;
-    row = row < rows ? row : rows - 1;
+    row = row_of(row < rows ? row : rows - 1);
     if (k < kend)
       R.v[i] = *reinterpret_cast<const uint4*>(X + (int64_t)row * ld + k);
     else
@@ -283,12 +284,16 @@ __global__ __launch_bounds__(NTHR, 2) void gemm_kernel(GemmArgs p) {
 #pragma unroll
     for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
+  // B's row behind output column n (GemmArgs::rope_rows)
+  auto weight_row = [&](int n) {
+    return EPI == EPI_STORE_ROPE && p.rope_rows ? rope_weight_row(n, p.rope_d, p.rope_cols) : n;
+  };
   Regs4 ra, rb;
   auto gload = [&](int k0) {
     if constexpr (AK) load_kmajor<T>(ra, A, p.lda, p.M, m0, k0, kend);
-    else load_kcontig<T>(ra, A, p.lda, p.M, m0, k0, kend);
+    else load_kcontig<T>(ra, A, p.lda, p.M, m0, k0, kend, [](int row) { return row; });
     if constexpr (BKM) load_kmajor<T>(rb, B, p.ldb, p.N, n0, k0, kend);
-    else load_kcontig<T>(rb, B, p.ldb, p.N, n0, k0, kend);
+    else load_kcontig<T>(rb, B, p.ldb, p.N, n0, k0, kend, weight_row);
   };
   auto lstore = [&](int buf) {
     if constexpr (AK) store_kmajor<T>(lds_a[buf], ra);
@@ -346,15 +351,16 @@ hipError_t dispatch_epi(const GemmArgs& a, int epi, hipStream_t s) {
 // K-contiguous operands need K % VEC == 0 and ld % VEC == 0; K-major operands need
 // their column count and ld to be multiples of VEC; all pointers 16-byte aligned.
 namespace {
-// The big kernels (bf16, M >= 512, N >= 256) have 16-byte vector epilogues only: every
-// output/aux row stride must keep 16-byte alignment, else the general kernel takes the
-// problem.
-bool takes_big(int dtype, int epi, const GemmArgs& a) {
-  if (!(dtype == DT_BF16 && a.M >= 512 && a.N >= 256 && a.N % 8 == 0)) return false;
+// The kernels of gemm_big.hip and gemm_small.hip fetch operands by 16-byte DMA and have
+// 16-byte vector epilogues only: every pointer and row stride must keep 16-byte alignment,
+// else the general kernel takes the problem.
+bool takes_tiled(int dtype, int epi, const GemmArgs& a) {
+  if (!(dtype == DT_BF16 && a.N % 8 == 0 && a.K > 0 && a.lda % 8 == 0 && a.ldb % 8 == 0))
+    return false;
   auto al16 = [](const void* q) { return (reinterpret_cast<uintptr_t>(q) & 15) == 0; };
   const bool f32out = epi == EPI_RESID || epi == EPI_F32;
   const int64_t vq = f32out ? 4 : 8;
-  return al16(a.C) && a.ldc % vq == 0 && (a.bias == nullptr || al16(a.bias)) &&
+  return al16(a.A) && al16(a.B) && al16(a.C) && a.ldc % vq == 0 && (a.bias == nullptr || al16(a.bias)) &&
          (a.aux == nullptr || (al16(a.aux) && a.ld_aux % (epi == EPI_RESID ? 4 : 8) == 0)) &&
          (a.C2 == nullptr || (al16(a.C2) && a.ldc2 % 8 == 0)) &&
          (epi != EPI_F32 || a.split_stride % 4 == 0);
@@ -376,14 +382,40 @@ bool takes_f32_small(const GemmArgs& a) {
 }
 }  // namespace
 
+namespace {
+// The tile gemm() runs a takes_tiled problem on.  (gemm_small.hip has the weight-gradient
+// layout with the fp32 epilogue only.)
+int tile_of(int layout, int epi, const GemmArgs& a) {
+  if (a.tile >= 0) return a.tile;
+  if (layout == GEMM_TN && epi != EPI_F32) return TILE_BIG;
+  return choose_tile(layout, a.M, a.N, a.K, a.kps > 0 ? (a.K + a.kps - 1) / a.kps : 1);
+}
+}  // namespace
+
 bool gemm_fused_colsum(int dtype, int layout, int epi, const GemmArgs& a) {
-  return layout == GEMM_NN && epi == EPI_GELU_BWD && a.kps <= 0 && takes_big(dtype, epi, a);
+  return layout == GEMM_NN && epi == EPI_GELU_BWD && a.kps <= 0 && takes_tiled(dtype, epi, a) &&
+         tile_of(layout, epi, a) == TILE_BIG;
+}
+
+int gemm_direct_tile(int dtype, int64_t M, int64_t N, int64_t K, const void* W, int64_t ldw) {
+  if ((reinterpret_cast<uintptr_t>(W) & 15) != 0 || dtype != DT_BF16 || ldw % 8 || N % 8)
+    return -1;
+  // a transposed copy costs its launch and one read and write of the weight at 4 TB/s
+  // (1280x1280 to 5120x5120 weights: 4 to 35 us); the large NN kernel then multiplies it
+  const int t = choose_tile(GEMM_NN, M, N, K, 1, 2000.0 + 4.0 * N * K / 4000.0);
+  return t == TILE_BIG ? -1 : t;
 }
 
 hipError_t gemm(int dtype, int layout, int epi, const GemmArgs& a, hipStream_t s) {
   if (a.M <= 0 || a.N <= 0) return hipSuccess;
   if (a.colsum && !gemm_fused_colsum(dtype, layout, epi, a)) return hipErrorInvalidValue;
-  if (takes_big(dtype, epi, a)) return gemm_big(layout, epi, a, s);
+  if (a.rope_rows && (layout != GEMM_NT || epi != EPI_STORE_ROPE || a.tile < 0))
+    return hipErrorInvalidValue;
+  if (takes_tiled(dtype, epi, a)) {
+    const int t = tile_of(layout, epi, a);
+    if (t != TILE_BIG) return gemm_small(layout, epi, t, a, s);
+    if (a.M >= 512 && a.N >= 256) return gemm_big(layout, epi, a, s);
+  }
   if (dtype == DT_BF16) {
     switch (layout) {
       case GEMM_NT: return dispatch_epi<bf16, false, false>(a, epi, s);

@@ -44,8 +44,16 @@ struct GemmArgs {
   const int32_t* rope_pos = nullptr;
   const float2* rope_tab = nullptr;
   int rope_d = 0, rope_cols = 0;
+  // NT with a tile from gemm_direct_tile only: B's rows are the weight's, in their original
+  // order (otherwise B is taken to be pair-interleaved already)
+  bool rope_rows = false;
+  int tile = -1;   // bf16: kernel tile (TILE_*, plan.h) chosen by the caller; -1: by size
 };
 hipError_t gemm(int dtype, int layout, int epi, const GemmArgs& a, hipStream_t s);
+// A Linear's forward product Y[M][N] = X W^T from the weight as stored, W [N][K] (row stride
+// ldw): the tile to pass as GemmArgs::tile with layout NT, or -1 where transposing W and
+// multiplying in layout NN is faster (or W is not aligned for direct reads).
+int gemm_direct_tile(int dtype, int64_t M, int64_t N, int64_t K, const void* W, int64_t ldw);
 // Whether gemm() runs this problem on the NN kernel that can write GemmArgs::colsum.
 bool gemm_fused_colsum(int dtype, int layout, int epi, const GemmArgs& a);
 // out[c] += sum of part[r][c] over r < rows, in a fixed order (two stages).
@@ -54,6 +62,9 @@ hipError_t partials_reduce(float* part, float* out, int64_t rows, int n, hipStre
 // stages) and TN; same contract as gemm()
 hipError_t gemm_big(int layout, int epi, const GemmArgs& a, hipStream_t s);
 
+// bf16 problems of few large tiles: tile TILE_64x64, TILE_64x128 or TILE_128x128 (plan.h),
+// the alignment rules of gemm_big, on any M and N; TN with EPI_F32 only
+hipError_t gemm_small(int layout, int epi, int tile, const GemmArgs& a, hipStream_t s);
 // fp32 problems of few 128x128 tiles: 32x32 tiles, K split over a block's waves; same
 // contract as gemm()
 hipError_t gemm_f32_small(int layout, int epi, const GemmArgs& a, hipStream_t s);

@@ -67,6 +67,14 @@ constexpr int kMaxGridSide = 32768;
 // backward blocks, column-sum chunks); the workspace holds this many rows per reduction.
 constexpr int64_t kPartialRowsMax = 1024;
 
+// Tiles of the bf16 GEMM kernels: those of gemm_small.hip, then the large ones of gemm_big.hip
+// (128x256 for NN, 256x256 for NT and TN).
+enum { TILE_64x64, TILE_64x128, TILE_128x128, TILE_BIG };
+// The tile that a bf16 product is expected to run fastest on.  layout as GEMM_*: 0 NT, 1 NN,
+// 2 TN; K is split `splits` ways.  big_extra_ns: what taking TILE_BIG costs besides.
+int choose_tile(int layout, int64_t M, int64_t N, int64_t K, int64_t splits,
+                double big_extra_ns = 0);
+
 struct GemmSplit {
   int splits = 1;
   int kps = 0;

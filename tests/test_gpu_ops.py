@@ -345,3 +345,37 @@ def test_gemm_f32_tiles(layout):
         mp.op_gemm(0, layout, E_F32, M, N, K, to_dev(A, "f32"), A.shape[1], to_dev(B, "f32"),
                    ldb, C, N, k_per_split=kps, split_stride=M * N)
         assert max_rel(host(C).sum(0), ref) < 2e-5, (M, N, K)
+
+
+@pytest.mark.parametrize("layout", [NT, NN, TN])
+def test_gemm_bf16_small_tiles(layout):
+    """bf16 products of few tiles at the edges of the 64x64, 64x128 and 128x128 kernels: K of
+    less than one 64-deep tile, with an odd remainder, of a ring's depth more or less, and
+    sizes on which each tile is the one chosen (2,560 x 1,280 runs 128x128, 1,408 x 1,280
+    64x128).  Products that the large kernel also runs have its K order, so their rows are the
+    same bits as those of a taller product (1,400 rows alone and within 6,000)."""
+    import paper_2607_03229_amd as mp
+    torch, dev = torch_dev()
+    rng = np.random.default_rng(60 + layout)
+    for (M, N, K) in [(1, 8, 8), (64, 64, 64), (65, 72, 136), (63, 56, 200), (200, 136, 264),
+                      (128, 128, 320), (130, 264, 456), (1408, 1280, 648), (2560, 1280, 136)]:
+        M = (M + 7) // 8 * 8 if layout == TN else M
+        announce(f"gemm bf16 small tiles layout={layout} M={M} N={N} K={K}")
+        A = rnd(rng, (K, M) if layout == TN else (M, K), "bf16")
+        B = rnd(rng, (N, K) if layout == NT else (K, N), "bf16")
+        C = nans((M, N), "f32")
+        mp.op_gemm(1, layout, E_F32, M, N, K, to_dev(A, "bf16"), A.shape[1], to_dev(B, "bf16"),
+                   B.shape[1], C, N)
+        assert max_rel(host(C), _ref_product(layout, A, B)) < 1e-5, (M, N, K)
+    if layout == TN:
+        return
+    M, N, K = 6000, 1280, 1000
+    announce(f"gemm bf16 rows of a taller product layout={layout}")
+    dA, dB = to_dev(rnd(rng, (M, K), "bf16"), "bf16"), to_dev(
+        rnd(rng, (N, K) if layout == NT else (K, N), "bf16"), "bf16")
+    out = []
+    for rows in (M, 1400, 200):
+        C = nans((rows, N), "f32")
+        mp.op_gemm(1, layout, E_F32, rows, N, K, dA, K, dB, dB.shape[1], C, N)
+        out.append(C)
+    assert all(torch.equal(out[0][:c.shape[0]], c) for c in out[1:])
