@@ -395,13 +395,25 @@ __global__ void splitk_reduce_kernel(const float* part, int splits, int64_t M, i
 }
 
 // ---- padding copy: dst[r][c] = c < K ? src[r][c] : 0, for c < Kp --------------------
-template <class T>
-__global__ void pad_cols_kernel(const T* src, int64_t rows, int K, T* dst, int Kp) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= rows * Kp) return;
-  const int64_t r = i / Kp;
-  const int c = (int)(i % Kp);
-  dst[i] = c < K ? src[r * K + c] : from_f<T>(0.f);
+// U: the unit both row lengths are multiples of (8 bytes where alignment allows, else one
+// element); a block's four waves take a row each, four units a lane in flight.  Bound by
+// memory: one element a thread with a division for its row took 28 us for 16,100 rows of 588
+// bf16 values (1.5 TB/s), this 10.6 us (3.7 TB/s).
+template <class U>
+__global__ __launch_bounds__(256) void pad_cols_kernel(const U* src, int64_t rows, int K, U* dst,
+                                                       int Kp) {
+  const int64_t r = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (r >= rows) return;
+  const U* s = src + r * K;
+  U* d = dst + r * Kp;
+  for (int c0 = threadIdx.x & 63; c0 < Kp; c0 += 256) {
+    U v[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = c0 + 64 * i < K ? s[c0 + 64 * i] : U{};
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (c0 + 64 * i < Kp) d[c0 + 64 * i] = v[i];
+  }
 }
 
 // ---- batched transpose: dst[c][r] = src[r][c], element bits copied ------------------
@@ -737,14 +749,17 @@ hipError_t splitk_reduce(const float* part, int splits, int64_t M, int64_t N, fl
 
 hipError_t pad_cols(int dtype, const void* src, int64_t rows, int K, void* dst, int Kp,
                     hipStream_t s) {
-  const int64_t n = rows * Kp;
-  if (n == 0) return hipSuccess;
-  if (dtype == DT_BF16)
-    hipLaunchKernelGGL(pad_cols_kernel<bf16>, dim3(blocks_for(n)), dim3(256), 0, s,
-                       (const bf16*)src, rows, K, (bf16*)dst, Kp);
-  else
-    hipLaunchKernelGGL(pad_cols_kernel<float>, dim3(blocks_for(n)), dim3(256), 0, s,
-                       (const float*)src, rows, K, (float*)dst, Kp);
+  if (rows * Kp == 0) return hipSuccess;
+  const int esz = dtype == DT_BF16 ? 2 : 4;
+  const uintptr_t al = (uintptr_t)src | (uintptr_t)dst | (uintptr_t)(K * esz) | (uintptr_t)(Kp * esz);
+  const unsigned grid = (unsigned)((rows + 3) / 4);
+#define MPIPE_PAD(U)                                                                          \
+  hipLaunchKernelGGL(pad_cols_kernel<U>, dim3(grid), dim3(256), 0, s, (const U*)src, rows,    \
+                     K * esz / (int)sizeof(U), (U*)dst, Kp * esz / (int)sizeof(U))
+  if (al % 8 == 0) MPIPE_PAD(uint2);
+  else if (esz == 4) MPIPE_PAD(uint32_t);
+  else MPIPE_PAD(uint16_t);
+#undef MPIPE_PAD
   return hipGetLastError();
 }
 

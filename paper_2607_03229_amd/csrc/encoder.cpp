@@ -303,25 +303,29 @@ AttnArgs attn_args(Ctx& x, const char* qkv, bool k_tiles) {
   return a;
 }
 
-// pointers of the padded patch matrix and patch-embedding weight
-void pe_operands(Ctx& x, const void* patches, const void*& Xp, const void*& Wpe, int64_t& ld) {
-  const Cfg& c = x.c;
-  if (c.kp != c.kpe) {
-    Xp = x.ws + x.P.ws_xp;
-    Wpe = x.ws + x.P.ws_wpe;
-    ld = c.kp;
-  } else {
-    Xp = patches;
-    Wpe = x.W(P_PE_W);
-    ld = c.kpe;
-  }
-}
+// The patch embedding's operands X [N][K] and W [h][K] (row stride ld).
+struct PatchOperands {
+  const void* X;
+  const void* W;
+  int64_t ld, K;
+};
 
-mpipe_status pad_pe(Ctx& x, const void* patches) {
+// They are multiplied as they lie when their rows keep 16-byte alignment; otherwise both are
+// copied into the workspace with rows zero-padded to a whole GEMM K step.  (At the Qwen2-VL
+// shape, 1,176 bf16 values a row, the copy of 27,568 patches took 81 us of a 3.2 ms pass, and
+// the product with its ragged K 1,176 is no slower than with 1,216.)
+mpipe_status patch_operands(Ctx& x, const void* patches, PatchOperands& o) {
   const Cfg& c = x.c;
-  if (c.kp == c.kpe) return MPIPE_OK;
+  const void* W = x.W(P_PE_W);
+  const bool aligned = ((reinterpret_cast<uintptr_t>(patches) | reinterpret_cast<uintptr_t>(W)) &
+                        15) == 0;
+  if (c.kp == c.kpe || (aligned && c.kpe * x.E % 16 == 0)) {
+    o = {patches, W, c.kpe, c.kpe};
+    return MPIPE_OK;
+  }
+  o = {x.ws + x.P.ws_xp, x.ws + x.P.ws_wpe, c.kp, c.kp};
   MP_CHECK(run(x.e, x.s, "pad", 0, [&] { return pad_cols(x.dt, patches, x.P.N, c.kpe, x.ws + x.P.ws_xp, c.kp, x.s); }));
-  MP_CHECK(run(x.e, x.s, "pad", 0, [&] { return pad_cols(x.dt, x.W(P_PE_W), c.hidden, c.kpe, x.ws + x.P.ws_wpe, c.kp, x.s); }));
+  MP_CHECK(run(x.e, x.s, "pad", 0, [&] { return pad_cols(x.dt, W, c.hidden, c.kpe, x.ws + x.P.ws_wpe, c.kp, x.s); }));
   return MPIPE_OK;
 }
 
@@ -406,17 +410,15 @@ mpipe_status forward(Ctx& x, const void* patches, void* merged, char* tape) {
   const int32_t* pos = reinterpret_cast<const int32_t*>(x.ws + P.ws_pos);
   const float* freq = reinterpret_cast<const float*>(x.ws + P.ws_rope);
 
-  MP_RET(pad_pe(x, patches));
-  const void *Xp, *Wpe;
-  int64_t ldx;
-  pe_operands(x, patches, Xp, Wpe, ldx);
+  PatchOperands pt;
+  MP_RET(patch_operands(x, patches, pt));
   char* h0 = c.layers > 0 ? base + act(0).hin : mbase + MS.hfin;
   {
-    FwdWeight pe{Wpe, h, c.kp, ldx};
+    FwdWeight pe{pt.W, h, pt.K, pt.ld};
     MP_RET(prepare_weights(x, &pe, 1, N));
     GemmArgs a;
     a.bias = x.W(P_PE_B);
-    MP_RET(linear_fwd(x, pe, EPI_RESID, Xp, ldx, N, h0, a));
+    MP_RET(linear_fwd(x, pe, EPI_RESID, pt.X, pt.ld, N, h0, a));
   }
   for (int l = 0; l < c.layers; ++l) {
     const ActSet& S = act(l);
@@ -548,12 +550,8 @@ mpipe_status backward(Ctx& x, const void* patches, const char* tape, const void*
   // Only the merger trainable: it is the trainable source (Lemma 1 applied to the
   // encoder's parts), so its backward ends with its own LayerNorm's affine gradients.
   const bool merger_only = P.mode == MODE_MERGER;
-  const void *Xp = nullptr, *Wpe = nullptr;
-  int64_t ldx = 0;
-  if (!merger_only) {
-    MP_RET(pad_pe(x, patches));
-    pe_operands(x, patches, Xp, Wpe, ldx);
-  }
+  PatchOperands pt{};
+  if (!merger_only) MP_RET(patch_operands(x, patches, pt));
 
   // Weight and bias gradients feed nothing else in the backward: they run on the side
   // stream (x.s2), which forks off after the gradient buffers they read are produced (in a
@@ -710,9 +708,9 @@ mpipe_status backward(Ctx& x, const void* patches, const char* tape, const void*
   // patch embedding (the trainable source: nothing goes upstream unless asked)
   MP_CHECK(ss.fork());   // dh, dht
   if (pending_qkv >= 0) MP_RET(qkv_dw(pending_qkv));
-  MP_RET(dw_gemm(x, dht, h, Xp, ldx, h, c.kpe, N, x.grad(dw, P_PE_W), c.kpe));
+  MP_RET(dw_gemm(x, dht, h, pt.X, pt.ld, h, c.kpe, N, x.grad(dw, P_PE_W), c.kpe));
   if (d_patches) {
-    GemmArgs a = ga(dht, h, Wpe, ldx, N, c.kpe, h, d_patches, c.kpe);
+    GemmArgs a = ga(dht, h, pt.W, pt.ld, N, c.kpe, h, d_patches, c.kpe);
     MP_RET(gemm_call(x, GEMM_NN, EPI_STORE, a));
   }
   return MPIPE_OK;

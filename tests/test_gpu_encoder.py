@@ -516,3 +516,35 @@ def test_merger_only_equals_full_backward_on_merger_full_size():
     np.testing.assert_array_equal(part_dw[ms], full_dw[ms])
     assert not part_dw[:ms.start].any()
     assert np.isfinite(part_dw[ms]).all() and part_dw[ms].any()
+
+
+@pytest.mark.parametrize("tpatch", [1, 2])
+def test_patch_rows_at_any_alignment(tpatch):
+    """Patch rows of 1,176 bf16 values are multiplied where they lie when they start on 16
+    bytes; rows of 588 values (8-byte multiples), and a buffer that starts 2 bytes later, go
+    through the padded copy.  Outputs and gradients do not depend on the route: bitwise."""
+    import paper_2607_03229_amd as mp
+    torch, dev = torch_dev()
+    cfg = mp.EncoderCfg(3, 14, tpatch, 128, 1, 2, 256, 2, 64, mp.BF16, 1e-6, 10000.0)
+    cu, grid = [0, 70 * 10], [(1, 70, 10)]
+    kpe, gen = 588 * tpatch, torch.Generator(device=dev).manual_seed(3)
+    announce(f"patch rows of {kpe} values, aligned and not")
+    enc = mp.Encoder(cfg)
+    s = enc.sizes(cu, grid, 1)
+    w = (torch.randn(enc.param_count(), device=dev, generator=gen) * 0.05).to(torch.bfloat16)
+    dm = torch.randn((175, 64), device=dev, generator=gen).to(torch.bfloat16)
+    x = torch.randn(700 * kpe, device=dev, generator=gen).to(torch.bfloat16)
+    shifted = torch.empty(700 * kpe + 8, dtype=torch.bfloat16, device=dev)[1:700 * kpe + 1]
+    shifted.copy_(x)
+    outs = []
+    for X in (x, shifted):
+        m, dx = torch.empty_like(dm), torch.empty_like(x)
+        dw = torch.zeros(w.numel(), dtype=torch.float32, device=dev)
+        ws = torch.empty(s["workspace"], dtype=torch.uint8, device=dev)
+        tape = torch.empty(s["tape"], dtype=torch.uint8, device=dev)
+        enc.fwd(w, X, cu, grid, 1, m, tape, ws)
+        enc.bwd(w, X, cu, grid, 1, tape, dm, dw, dx, ws)
+        outs.append((m, dw, dx))
+    torch.cuda.synchronize()
+    assert torch.isfinite(outs[0][1]).all() and outs[0][1].any()
+    assert all(torch.equal(a, b) for a, b in zip(*outs))
