@@ -375,10 +375,8 @@ namespace {
 // (144) 328 / 343, 2048x1536x384 (192) 44 / 44, 2048x2048x2048 (256) 170 / 288.  The two
 // kernels add a product's K terms in different orders.
 constexpr int64_t F32_SMALL_TILES = 128;
-bool takes_f32_small(const GemmArgs& a) {
-  const int64_t tiles = (int64_t)((a.M + BM - 1) / BM) * ((a.N + BN - 1) / BN);
-  const int64_t splits = a.kps > 0 ? (a.K + a.kps - 1) / a.kps : 1;
-  return tiles * splits <= F32_SMALL_TILES;
+bool f32_small_tiles(int64_t M, int64_t N, int64_t splits) {
+  return (M + BM - 1) / BM * ((N + BN - 1) / BN) * splits <= F32_SMALL_TILES;
 }
 }  // namespace
 
@@ -398,8 +396,11 @@ bool gemm_fused_colsum(int dtype, int layout, int epi, const GemmArgs& a) {
 }
 
 int gemm_direct_tile(int dtype, int64_t M, int64_t N, int64_t K, const void* W, int64_t ldw) {
-  if ((reinterpret_cast<uintptr_t>(W) & 15) != 0 || dtype != DT_BF16 || ldw % 8 || N % 8)
-    return -1;
+  const int vec = dtype == DT_BF16 ? 8 : 4;
+  if ((reinterpret_cast<uintptr_t>(W) & 15) != 0 || ldw % vec || K % vec || N % 8) return -1;
+  // fp32: the 32x32 kernel reads a K-contiguous weight as fast as a K-major one, so its
+  // transposed copy (4 to 9 us a layer of the small encoders) buys nothing
+  if (dtype == DT_F32) return f32_small_tiles(M, N, 1) ? 0 : -1;
   // a transposed copy costs its launch and one read and write of the weight at 4 TB/s
   // (1280x1280 to 5120x5120 weights: 4 to 35 us); the large NN kernel then multiplies it
   const int t = choose_tile(GEMM_NN, M, N, K, 1, 2000.0 + 4.0 * N * K / 4000.0);
@@ -423,7 +424,8 @@ hipError_t gemm(int dtype, int layout, int epi, const GemmArgs& a, hipStream_t s
       case GEMM_TN: return dispatch_epi<bf16, true, true>(a, epi, s);
     }
   } else {
-    if (takes_f32_small(a)) return gemm_f32_small(layout, epi, a, s);
+    if (f32_small_tiles(a.M, a.N, a.kps > 0 ? (a.K + a.kps - 1) / a.kps : 1))
+      return gemm_f32_small(layout, epi, a, s);
     switch (layout) {
       case GEMM_NT: return dispatch_epi<float, false, false>(a, epi, s);
       case GEMM_NN: return dispatch_epi<float, false, true>(a, epi, s);

@@ -35,9 +35,10 @@ struct Frag {
 };
 
 // rows (columns, when KM) r0.. of an operand at K step k0: zero past kend, clamped rows
-template <bool KM>
+// (row_of: the row to read for tile row `row`)
+template <bool KM, class RowOf>
 __device__ __forceinline__ void load_frag(Frag& F, const float* X, int64_t ld, int rows, int r0,
-                                          int k0, int kend, int g, int r) {
+                                          int k0, int kend, int g, int r, RowOf row_of) {
   const int k = k0 + 4 * g;
   if constexpr (KM) {
     int c = r0 + 2 * r;
@@ -53,7 +54,7 @@ __device__ __forceinline__ void load_frag(Frag& F, const float* X, int64_t ld, i
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
       int row = r0 + 16 * i + r;
-      row = row < rows ? row : rows - 1;
+      row = row_of(row < rows ? row : rows - 1);
       float4 x = make_float4(0.f, 0.f, 0.f, 0.f);
       if (k < kend) x = *reinterpret_cast<const float4*>(X + (int64_t)row * ld + k);
       F.v[i][0] = x.x;
@@ -162,12 +163,17 @@ __global__ __launch_bounds__(NTHR) void gemm_f32_kernel(GemmArgs p) {
   for (int i = 0; i < 2; ++i)
 #pragma unroll
     for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  auto a_row = [](int row) { return row; };
+  // B's row behind output column n (GemmArgs::rope_rows)
+  auto b_row = [&](int n) {
+    return EPI == EPI_STORE_ROPE && p.rope_rows ? rope_weight_row(n, p.rope_d, p.rope_cols) : n;
+  };
   Frag a[AHEAD], b[AHEAD];
 #pragma unroll
   for (int u = 0; u < AHEAD; ++u)
     if (u < nt) {
-      load_frag<AK>(a[u], A, p.lda, p.M, m0, kbeg + u * BK, kend, g, r);
-      load_frag<BKM>(b[u], B, p.ldb, p.N, n0, kbeg + u * BK, kend, g, r);
+      load_frag<AK>(a[u], A, p.lda, p.M, m0, kbeg + u * BK, kend, g, r, a_row);
+      load_frag<BKM>(b[u], B, p.ldb, p.N, n0, kbeg + u * BK, kend, g, r, b_row);
     }
   for (int t = 0; t < nt; t += AHEAD)
 #pragma unroll
@@ -183,8 +189,8 @@ __global__ __launch_bounds__(NTHR) void gemm_f32_kernel(GemmArgs p) {
                                                                acc[i][j], 0, 0, 0);
         if (t + u + AHEAD < nt) {
           const int k0 = kbeg + (t + u + AHEAD) * BK;
-          load_frag<AK>(a[u], A, p.lda, p.M, m0, k0, kend, g, r);
-          load_frag<BKM>(b[u], B, p.ldb, p.N, n0, k0, kend, g, r);
+          load_frag<AK>(a[u], A, p.lda, p.M, m0, k0, kend, g, r, a_row);
+          load_frag<BKM>(b[u], B, p.ldb, p.N, n0, k0, kend, g, r, b_row);
         }
       }
   // sub-tile (i, j), element (4g + v, r): tile row and column by operand form
