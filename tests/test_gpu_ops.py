@@ -379,3 +379,24 @@ def test_gemm_bf16_small_tiles(layout):
         mp.op_gemm(1, layout, E_F32, rows, N, K, dA, K, dB, dB.shape[1], C, N)
         out.append(C)
     assert all(torch.equal(out[0][:c.shape[0]], c) for c in out[1:])
+
+
+@pytest.mark.parametrize("rows", [1, 4, 60, 66, 2048, 2052, 5000])
+def test_affine_gradient_partials(rows):
+    """The LayerNorm affine gradients are reduced from one partial row per block: 1, a wave's
+    share more or less, 512 (the most that one launch takes), 513 and 1,024 partial rows.
+    Sums of up to 5,000 fp32 terms in any order: 1e-5 of the largest."""
+    import paper_2607_03229_amd as mp
+    torch, dev = torch_dev()
+    rng, n = np.random.default_rng(rows), 132
+    announce(f"affine gradient partials rows={rows}")
+    X, dY = rng.standard_normal((2, rows, n)).astype(np.float32)
+    mean, rstd = X.mean(1), 1 / np.sqrt(X.astype(np.float64).var(1) + 1e-6)
+    gg, gb = to_dev(np.ones(n), "f32"), to_dev(np.zeros(n), "f32")
+    scratch = torch.empty(mp.op_scratch_bytes(rows, 1, n, 0), dtype=torch.uint8, device=dev)
+    tm, tr = to_dev(mean, "f32"), to_dev(rstd, "f32")
+    mp.op_layernorm_bwd(0, to_dev(dY, "f32"), to_dev(X, "f32"), tm, tr, to_dev(np.ones(n), "f32"),
+                        rows, n, None, None, None, gg, gb, scratch)
+    xhat = (X - host(tm)[:, None]) * host(tr)[:, None]
+    assert max_rel(host(gg), 1 + (dY * xhat).sum(0)) < 1e-5
+    assert max_rel(host(gb), dY.astype(np.float64).sum(0)) < 1e-5
