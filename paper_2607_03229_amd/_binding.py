@@ -237,7 +237,8 @@ class Encoder:
         return dict(zip(keys, list(out)))
 
     def set_side_stream(self, enable: bool):
-        """Backward weight-gradient work on the handle's internal stream (default) or not."""
+        """Backward weight-gradient work on the handle's internal stream or not (default: on
+        it where the micro-batch is large enough to gain)."""
         _check(self.L.mpipe_encoder_set_side_stream(self._h, int(enable)))
 
     # -- kernel timing --

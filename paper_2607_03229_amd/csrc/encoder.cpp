@@ -54,7 +54,7 @@ struct mpipe_encoder {
   std::vector<hipEvent_t> pool;
   // Weight-gradient side stream of the backward (default priority) and its sync events:
   // 0 fork (caller -> side), 1..7 buffer-free signals (side -> caller), 8 join.
-  bool side_on = true;
+  int side_mode = -1;   // mpipe_encoder_set_side_stream; -1: by size (side_pays)
   hipStream_t side = nullptr;
   int side_dev = -1;
   hipEvent_t sync[9] = {};
@@ -261,6 +261,13 @@ hipError_t ensure_side(mpipe_encoder* e) {
   e->side_dev = dev;
   return hipSuccess;
 }
+
+// Whether the backward's weight-gradient work is worth a stream of its own.  Each hand-off
+// between the streams costs some microseconds of events and waits (22 in a two-layer step),
+// which the overlap must give back.  Measured on MI355X, us per trained two-layer step on /
+// off (rows x hidden): fp32 164x128 514 / 287, 1040x384 988 / 974, bf16 256x1024 802 / 774;
+// 1408x1280 1492 / 1587, 2048x1024 1368 / 1416, 10528x1024 3869 / 4027.
+bool side_pays(const Cfg& c, const Plan& P) { return P.N * c.hidden >= (int64_t)1 << 20; }
 
 mpipe_status upload_meta(mpipe_encoder* e, const Plan& P, char* ws, hipStream_t s) {
   const size_t bytes = P.meta_bytes;
@@ -762,7 +769,7 @@ void mpipe_encoder_destroy(mpipe_encoder* e) {
 
 mpipe_status mpipe_encoder_set_side_stream(mpipe_encoder* e, int32_t enable) {
   MP_RET(check_handle(e));
-  e->side_on = enable != 0;
+  e->side_mode = enable != 0;
   return MPIPE_OK;
 }
 
@@ -902,7 +909,7 @@ mpipe_status mpipe_encoder_bwd(mpipe_encoder* e, const void* weights, const void
   Ctx x{e, e->cfg, P, s, reinterpret_cast<const char*>(weights), reinterpret_cast<char*>(ws),
         e->cfg.dtype, e->cfg.esz};
   x.s2 = s;
-  if (e->side_on) {
+  if (e->side_mode > 0 || (e->side_mode < 0 && side_pays(e->cfg, P))) {
     MP_CHECK(ensure_side(e));
     x.s2 = e->side;
   }
