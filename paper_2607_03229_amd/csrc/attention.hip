@@ -24,13 +24,14 @@
 namespace mpipe {
 namespace {
 
-// 16-row sub-tiles per wave (NS) of the bf16 kernels; a 128-row work tile takes 8 / NS
-// waves.  NS = 4 reuses each LDS fragment over four MFMAs (half the LDS traffic of NS = 2)
-// at one wave per SIMD; NS = 2 runs several blocks of four waves per CU: three for the
-// forward and dQ kernels (two-stage tile rings, 48 KB of LDS and at most 168 registers per
-// wave; measured 7.5 % and 1 % faster than two blocks with three-stage rings), two for
-// dK/dV (three-stage ring, over 200 registers).
-constexpr int FWD_NS = 2, DQ_NS = 2, DKDV_NS = 2;
+// The bf16 kernels run blocks of NW waves with NS 16-row sub-tiles each.  NS = 2, a whole
+// work item per block, uses each LDS fragment twice and runs several blocks per CU: three
+// for the forward and dQ kernels (two-stage tile rings, 48 KB of LDS and at most 168
+// registers per wave; measured 7.5 % and 1 % faster than two blocks with three-stage rings),
+// two for dK/dV (three-stage ring, over 200 registers).  NS = 1, half a work item per block
+// (the same values bit for bit), is for micro-batches of few work items, where a block's
+// own chain of tiles is what takes the time: see small_pairs.
+constexpr int NW = 4;
 
 template <int D> struct AD {
   static constexpr int NC = D / 8;                          // 16-byte chunks per row
@@ -226,13 +227,14 @@ __device__ __forceinline__ bf16x8 frag_trt(const uint4* tile, int kb, int c0, in
 // multiply per accumulator) runs on a few tiles instead of most.  Row sums of the bf16
 // weights come from the PV MFMAs themselves, with a ones operand in place of V.
 template <int D, int NS>
-__global__ __launch_bounds__(64 * (8 / NS), NS == 2 ? 3 : 1) void attn_fwd_kernel(AttnArgs p) {
-  constexpr int NW = 8 / NS, RW = 16 * NS;   // waves per block, rows per wave
+__global__ __launch_bounds__(64 * NW, NS == 2 ? 3 : 2) void attn_fwd_kernel(AttnArgs p) {
+  constexpr int RW = 16 * NS, SUB = 2 / NS;   // rows per wave, blocks per work item
   constexpr int NDT = AD<D>::NDT, SL = TG<D, NW>::SLOTS;
   __shared__ uint4 k0s[SL], k1s[SL], v0s[SL], v1s[SL];
-  const int work = blockIdx.x / p.heads, head = blockIdx.x % p.heads;
+  const int work = blockIdx.x / (SUB * p.heads), head = blockIdx.x % p.heads;
   const int4 wk = p.work[work];
-  const int q0 = wk.x, s0 = wk.y, s1 = wk.z;
+  const int q0 = wk.x + NW * RW * (blockIdx.x / p.heads % SUB), s0 = wk.y, s1 = wk.z;
+  if (q0 >= s1) return;
   const int w = threadIdx.x >> 6, l = threadIdx.x & 63, g = l >> 4, r = l & 15;
   const bf16* Q = reinterpret_cast<const bf16*>(p.q) + head * D;
   const bf16* K = reinterpret_cast<const bf16*>(p.k) + head * D;
@@ -380,14 +382,15 @@ __global__ __launch_bounds__(64 * (8 / NS), NS == 2 ? 3 : 1) void attn_fwd_kerne
 // Per 128-key tile (32 keys per wave), 3-stage pipeline over 64-query tiles of Q, dO,
 // LSE and delta.
 template <int D, int NS>
-__global__ __launch_bounds__(64 * (8 / NS), NS == 2 ? 2 : 1) void attn_bwd_dkdv_kernel(AttnArgs p) {
-  constexpr int NW = 8 / NS, RW = 16 * NS;   // waves per block, rows per wave
+__global__ __launch_bounds__(64 * NW, 2) void attn_bwd_dkdv_kernel(AttnArgs p) {
+  constexpr int RW = 16 * NS, SUB = 2 / NS;   // rows per wave, blocks per work item
   constexpr int NDT = AD<D>::NDT, SL = TG<D, NW>::SLOTS, NI = TG<D, NW>::NI;
   __shared__ uint4 q0s[SL], q1s[SL], q2s[SL], d0s[SL], d1s[SL], d2s[SL];
   __shared__ __attribute__((aligned(16))) float l0s[64], l1s[64], l2s[64], e0s[64], e1s[64], e2s[64];
-  const int work = blockIdx.x / p.heads, head = blockIdx.x % p.heads;
+  const int work = blockIdx.x / (SUB * p.heads), head = blockIdx.x % p.heads;
   const int4 wk = p.work[work];
-  const int k0 = wk.x, s0 = wk.y, s1 = wk.z;
+  const int k0 = wk.x + NW * RW * (blockIdx.x / p.heads % SUB), s0 = wk.y, s1 = wk.z;
+  if (k0 >= s1) return;
   const int w = threadIdx.x >> 6, l = threadIdx.x & 63, g = l >> 4, r = l & 15;
   const bf16* Q = reinterpret_cast<const bf16*>(p.q) + head * D;
   const bf16* K = reinterpret_cast<const bf16*>(p.k) + head * D;
@@ -545,13 +548,14 @@ __global__ __launch_bounds__(64 * (8 / NS), NS == 2 ? 2 : 1) void attn_bwd_dkdv_
 
 // ---- backward: dQ (and delta) --------------------------------------------------------
 template <int D, int NS>
-__global__ __launch_bounds__(64 * (8 / NS), NS == 2 ? 3 : 1) void attn_bwd_dq_kernel(AttnArgs p) {
-  constexpr int NW = 8 / NS, RW = 16 * NS;   // waves per block, rows per wave
+__global__ __launch_bounds__(64 * NW, NS == 2 ? 3 : 2) void attn_bwd_dq_kernel(AttnArgs p) {
+  constexpr int RW = 16 * NS, SUB = 2 / NS;   // rows per wave, blocks per work item
   constexpr int NDT = AD<D>::NDT, SL = TG<D, NW>::SLOTS;
   __shared__ uint4 k0s[SL], k1s[SL], v0s[SL], v1s[SL];
-  const int work = blockIdx.x / p.heads, head = blockIdx.x % p.heads;
+  const int work = blockIdx.x / (SUB * p.heads), head = blockIdx.x % p.heads;
   const int4 wk = p.work[work];
-  const int q0 = wk.x, s0 = wk.y, s1 = wk.z;
+  const int q0 = wk.x + NW * RW * (blockIdx.x / p.heads % SUB), s0 = wk.y, s1 = wk.z;
+  if (q0 >= s1) return;
   const int w = threadIdx.x >> 6, l = threadIdx.x & 63, g = l >> 4, r = l & 15;
   const bf16* Q = reinterpret_cast<const bf16*>(p.q) + head * D;
   const bf16* K = reinterpret_cast<const bf16*>(p.k) + head * D;
@@ -1052,19 +1056,36 @@ __global__ __launch_bounds__(256) void attn_bwd_dkdv_f32_kernel(AttnArgs p) {
                     dk);
 }
 
+// bf16: up to one (work item, head) pair per CU (256) a pair is dealt to two blocks, which
+// otherwise leave CUs idle while each wave walks its two sub-tiles; past that the second use
+// of a fragment is worth more.  Measured on MI355X, us a pass, whole items -> halves: 32 frozen
+// layers at 256 rows x 16 heads of 80 (32 pairs) 2873 -> 2812, two at 768 rows x 16 of 64 (96)
+// 265.5 -> 255.7, two trained at 1,408 rows x 16 of 80 (176) 1537 -> 1518.
+constexpr int64_t SMALL_PAIRS = 256;
+bool small_pairs(const AttnArgs& a) { return (int64_t)a.n_work * a.heads <= SMALL_PAIRS; }
+
 template <int D>
 hipError_t fwd_bf16(const AttnArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL((attn_fwd_kernel<D, FWD_NS>), dim3(a.n_work * a.heads), dim3(64 * (8 / FWD_NS)), 0, s, a);
+  if (small_pairs(a))
+    hipLaunchKernelGGL((attn_fwd_kernel<D, 1>), dim3(2 * a.n_work * a.heads), dim3(64 * NW), 0, s, a);
+  else
+    hipLaunchKernelGGL((attn_fwd_kernel<D, 2>), dim3(a.n_work * a.heads), dim3(64 * NW), 0, s, a);
   return hipGetLastError();
 }
 template <int D>
 hipError_t dq_bf16(const AttnArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL((attn_bwd_dq_kernel<D, DQ_NS>), dim3(a.n_work * a.heads), dim3(64 * (8 / DQ_NS)), 0, s, a);
+  if (small_pairs(a))
+    hipLaunchKernelGGL((attn_bwd_dq_kernel<D, 1>), dim3(2 * a.n_work * a.heads), dim3(64 * NW), 0, s, a);
+  else
+    hipLaunchKernelGGL((attn_bwd_dq_kernel<D, 2>), dim3(a.n_work * a.heads), dim3(64 * NW), 0, s, a);
   return hipGetLastError();
 }
 template <int D>
 hipError_t dkdv_bf16(const AttnArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL((attn_bwd_dkdv_kernel<D, DKDV_NS>), dim3(a.n_work * a.heads), dim3(64 * (8 / DKDV_NS)), 0, s, a);
+  if (small_pairs(a))
+    hipLaunchKernelGGL((attn_bwd_dkdv_kernel<D, 1>), dim3(2 * a.n_work * a.heads), dim3(64 * NW), 0, s, a);
+  else
+    hipLaunchKernelGGL((attn_bwd_dkdv_kernel<D, 2>), dim3(a.n_work * a.heads), dim3(64 * NW), 0, s, a);
   return hipGetLastError();
 }
 template <int D>

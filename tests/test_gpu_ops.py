@@ -321,6 +321,42 @@ def test_attention_f32_tile_edges(heads, d):
     assert max(errs) < 1e-5, errs
 
 
+@pytest.mark.parametrize("d", [32, 64, 80])
+def test_attention_bf16_half_items(d):
+    """Micro-batches of up to 256 (work item, head) pairs deal each pair to two blocks of 64
+    rows: segments at the edges of 16, 64 and 128 rows on that path against the oracle, and
+    the same segments ten times over (360 pairs, a block per pair) bit for bit, since a
+    row's value may not depend on what shares its micro-batch."""
+    import paper_2607_03229_amd as mp
+    torch, dev = torch_dev()
+    lens, heads = [1, 15, 16, 17, 63, 64, 65, 79, 127, 128, 129, 145, 193, 256], 2
+    h, n = heads * d, sum(lens)
+    rng = np.random.default_rng(60 + d)
+    qkv, dO = rnd(rng, (n, 3 * h), "bf16", 1.5), rnd(rng, (n, h), "bf16")
+    out = []
+    for reps in (1, 10):
+        cu = np.concatenate([[0], np.cumsum(lens * reps)]).astype(np.int32)
+        N = n * reps
+        announce(f"bf16 attention half items d={d} N={N}")
+        o, lse, dqkv = nans((N, h), "bf16"), nans((heads, N), "f32"), nans((N, 3 * h), "bf16")
+        scratch = torch.empty(mp.op_scratch_bytes(N, heads, h, len(lens) * reps),
+                              dtype=torch.uint8, device=dev)
+        tq, tdo = to_dev(np.tile(qkv, (reps, 1)), "bf16"), to_dev(np.tile(dO, (reps, 1)), "bf16")
+        mp.op_attention_fwd(_dt("bf16"), tq, N, heads, d, cu, o, lse, scratch)
+        mp.op_attention_bwd(_dt("bf16"), tq, o, tdo, lse, N, heads, d, cu, dqkv, scratch)
+        out.append([host(o), host(lse).T, host(dqkv)])
+    for one, ten in zip(*out):
+        assert np.array_equal(np.tile(one, (10, 1)), ten)
+    q, k, v = qkv[:, :h], qkv[:, h:2 * h], qkv[:, 2 * h:]
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    ro, rlse = oracle.attention(q, k, v, cu, heads, d)
+    ref = oracle.attention_bwd(q, k, v, ro, dO, rlse, cu, heads, d)
+    o, lse, got = out[0]
+    errs = [max_rel(o, ro)] + [max_rel(got[:, i * h:(i + 1) * h], ref[i]) for i in range(3)]
+    assert max(errs) < 2e-2, errs
+    assert max_rel(lse, rlse) < 1e-3
+
+
 @pytest.mark.parametrize("layout", [NT, NN, TN])
 def test_gemm_f32_tiles(layout):
     """fp32 products at the edges of the 32x32 kernel (a K of less than one 16-deep step, of
