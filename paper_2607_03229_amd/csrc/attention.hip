@@ -864,12 +864,13 @@ __global__ __launch_bounds__(256) void attn_fwd_f32_kernel(AttnArgs p) {
     float mx = fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3]));
     mx = fmaxf(mx, __shfl_xor(mx, 16));
     mx = fmaxf(mx, __shfl_xor(mx, 32));
-    const float mn = fmaxf(m, mx), a = expf(m - mn);
+    // a wave whose scores are all -inf so far has no maximum to subtract: its terms are 0
+    const float mn = fmaxf(m, mx), ref = mn == -INFINITY ? 0.f : mn, a = expf(m - ref);
     m = mn;
     sum *= a;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      s[e] = expf(s[e] - mn);
+      s[e] = expf(s[e] - ref);
       sum += s[e];   // this lane's keys; the lane groups are added after the loop
     }
 #pragma unroll
@@ -883,7 +884,7 @@ __global__ __launch_bounds__(256) void attn_fwd_f32_kernel(AttnArgs p) {
   ml[w][l] = make_float2(m, sum);
   __syncthreads();
   // wave 0 always has a tile, so the common maximum is a real score's; a wave without
-  // tiles has weight 0
+  // tiles, or with scores of -inf only, has weight 0
   float M = ml[0][l].x, tot = 0.f;
 #pragma unroll
   for (int i = 1; i < 4; ++i) M = fmaxf(M, ml[i][l].x);

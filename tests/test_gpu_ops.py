@@ -436,3 +436,36 @@ def test_affine_gradient_partials(rows):
     xhat = (X - host(tm)[:, None]) * host(tr)[:, None]
     assert max_rel(host(gg), 1 + (dY * xhat).sum(0)) < 1e-5
     assert max_rel(host(gb), dY.astype(np.float64).sum(0)) < 1e-5
+
+
+def test_attention_f32_scores_of_minus_infinity():
+    """Scores that overflow to -inf have weight 0 and leave the others' softmax alone, also
+    where one wave of the fp32 forward (tiles w, w + 4, ... of 16 keys) meets nothing else:
+    all of wave 1's keys, wave 2's first tile and one key of wave 3 here.  Against the oracle,
+    which holds the scores in 64 bits; 1e-5 as for the other fp32 attention tests."""
+    import paper_2607_03229_amd as mp
+    torch, dev = torch_dev()
+    heads, d, N = 2, 32, 200
+    h = heads * d
+    rng = np.random.default_rng(5)
+    announce(f"fp32 attention with scores of -inf heads={heads} d={d} N={N}")
+    qkv, dO = rnd(rng, (N, 3 * h), "f32", 1.5), rnd(rng, (N, h), "f32")
+    first = np.arange(heads) * d                       # component 0 of each head
+    keys = [j for j in range(N) if j // 16 % 4 == 1 or j // 16 == 2 or j == 50]
+    qkv[:, first] = 1e20
+    qkv[:, h + first] = 0.0
+    qkv[np.ix_(keys, h + first)] = -1e20               # 1e20 * -1e20 overflows
+    q, k, v = qkv[:, :h], qkv[:, h:2 * h], qkv[:, 2 * h:]
+    cu = np.array([0, N], np.int32)
+    ro, rlse = oracle.attention(q, k, v, cu, heads, d)
+    ref = oracle.attention_bwd(q, k, v, ro, dO, rlse, cu, heads, d)
+    o, lse, dqkv = nans((N, h), "f32"), nans((heads, N), "f32"), nans((N, 3 * h), "f32")
+    scratch = torch.empty(mp.op_scratch_bytes(N, heads, h, 1), dtype=torch.uint8, device=dev)
+    tq = to_dev(qkv, "f32")
+    mp.op_attention_fwd(0, tq, N, heads, d, cu, o, lse, scratch)
+    mp.op_attention_bwd(0, tq, o, to_dev(dO, "f32"), lse, N, heads, d, cu, dqkv, scratch)
+    got = host(dqkv)
+    rest = np.setdiff1d(np.arange(h), first)           # (dK's component 0 is 1e20 times dS)
+    errs = [max_rel(host(o), ro), max_rel(host(lse), rlse.T), max_rel(got[:, :h], ref[0]),
+            max_rel(got[:, h + rest], ref[1][:, rest]), max_rel(got[:, 2 * h:], ref[2])]
+    assert max(errs) < 1e-5, errs
