@@ -10,8 +10,8 @@
 // Tiling (gfx950): 256 threads = 4 wave64 in a 2x2 grid, block tile 128x128,
 // K step 64 (bf16) / 32 (fp32), each wave owns a 64x64 tile of 4x4 16x16
 // accumulators.  bf16 uses v_mfma_f32_16x16x32_bf16; fp32 uses
-// v_mfma_f32_16x16x4_f32 (eight per 32-wide K step; products of few tiles take the kernel
-// of gemm_f32.hip).  LDS is double-buffered
+// v_mfma_f32_16x16x4_f32 (eight per 32-wide K step, in the K order of gemm_f32.hip, whose
+// kernel takes products of few tiles).  LDS is double-buffered
 // (64 KB); the next tile's global loads are in flight during the MFMAs.
 // Blocks are remapped so that consecutive tiles land on the same XCD and walk
 // the output in groups of 8 tile-rows (L2 reuse of A rows and B columns).
@@ -155,32 +155,27 @@ template <> struct Mma<bf16> {
 };
 
 template <> struct Mma<float> {
-  // one 32-wide K step: lane group g holds k = 8g..8g+7 (two chunks); the eight
-  // 16x16x4 MFMAs take slot s = those k's in order (same mapping for A and B).
+  // 16-deep half `kk` of a 32-deep stage: lane group g holds k = 4g .. 4g + 3 of it (one
+  // chunk), the operands of four successive 16x16x4 MFMAs (same mapping for A and B).
   static __device__ __forceinline__ void run(const uint4* As, const uint4* Bs, int wm, int wn,
-                                             f32x4 (&acc)[4][4]) {
+                                             int kk, f32x4 (&acc)[4][4]) {
     const int l = threadIdx.x & 63;
     const int g = l >> 4, r = l & 15;
-    float a[4][8], b[4][8];
+    float a[4][4], b[4][4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const int ra = wm * 64 + 16 * i + r, rb = wn * 64 + 16 * i + r;
-      uint4 a0 = As[swz(ra, 2 * g)], a1 = As[swz(ra, 2 * g + 1)];
-      uint4 b0 = Bs[swz(rb, 2 * g)], b1 = Bs[swz(rb, 2 * g + 1)];
-      const float* pa0 = reinterpret_cast<const float*>(&a0);
-      const float* pa1 = reinterpret_cast<const float*>(&a1);
-      const float* pb0 = reinterpret_cast<const float*>(&b0);
-      const float* pb1 = reinterpret_cast<const float*>(&b1);
+      const uint4 va = As[swz(wm * 64 + 16 * i + r, kk * 4 + g)];
+      const uint4 vb = Bs[swz(wn * 64 + 16 * i + r, kk * 4 + g)];
+      const float* pa = reinterpret_cast<const float*>(&va);
+      const float* pb = reinterpret_cast<const float*>(&vb);
 #pragma unroll
       for (int s = 0; s < 4; ++s) {
-        a[i][s] = pa0[s];
-        a[i][s + 4] = pa1[s];
-        b[i][s] = pb0[s];
-        b[i][s + 4] = pb1[s];
+        a[i][s] = pa[s];
+        b[i][s] = pb[s];
       }
     }
 #pragma unroll
-    for (int s = 0; s < 8; ++s)
+    for (int s = 0; s < 4; ++s)
 #pragma unroll
       for (int i = 0; i < 4; ++i)
 #pragma unroll
@@ -279,10 +274,23 @@ __global__ __launch_bounds__(NTHR, 2) void gemm_kernel(GemmArgs p) {
   const int wm = w >> 1, wn = w & 1;
 
   f32x4 acc[4][4];
+  auto clear = [](f32x4 (&x)[4][4]) {
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < 4; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int j = 0; j < 4; ++j) x[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  };
+  clear(acc);
+  // fp32 products of rows (NT, NN) sum K in the order of the 32x32 kernel of gemm_f32.hip: a
+  // chain for each of four quarters (whole 16-deep steps), the quarters in order, so that a
+  // row has the same bits from either kernel, whatever else its product holds.  (Costs the 64
+  // registers of `total` and 1 to 2.4 % against one chain: 2048x2048x2048 NN 171 -> 173 us,
+  // 4096x1536x384 85.6 -> 87.6.)
+  constexpr bool QUARTERS = std::is_same<T, float>::value && !AK;
+  [[maybe_unused]] f32x4 total[4][4];
+  [[maybe_unused]] const int quarter = ((kend - kbeg + 15) / 16 + 3) / 4;
+  [[maybe_unused]] int left = quarter;
+  if constexpr (QUARTERS) clear(total);
 
   // B's row behind output column n (GemmArgs::rope_rows)
   auto weight_row = [&](int n) {
@@ -309,10 +317,33 @@ __global__ __launch_bounds__(NTHR, 2) void gemm_kernel(GemmArgs p) {
     for (int kt = 0; kt < nk; ++kt) {
       const int cur = kt & 1;
       if (kt + 1 < nk) gload(kbeg + (kt + 1) * BK);
-      Mma<T>::run(lds_a[cur], lds_b[cur], wm, wn, acc);
+      if constexpr (std::is_same<T, float>::value) {
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk) {
+          Mma<T>::run(lds_a[cur], lds_b[cur], wm, wn, kk, acc);
+          if constexpr (QUARTERS) {
+            if (--left == 0) {
+#pragma unroll
+              for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) total[i][j] += acc[i][j];
+              clear(acc);
+              left = quarter;
+            }
+          }
+        }
+      } else {
+        Mma<T>::run(lds_a[cur], lds_b[cur], wm, wn, acc);
+      }
       if (kt + 1 < nk) lstore(cur ^ 1);
       __syncthreads();
     }
+  }
+  if constexpr (QUARTERS) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) acc[i][j] = total[i][j] + acc[i][j];
   }
   epilogue<T, EPI>(p, split, m0 + wm * 64, n0 + wn * 64, acc);
 }
@@ -372,8 +403,9 @@ namespace {
 // sixteen times the blocks and four waves to a tile's K; with more tiles the larger tile's
 // reuse wins.  Measured on MI355X, us, 128x128 / 32x32 (M x N x K, tiles): 1040x1536x384
 // (108) 42 / 26, 4096x384x1536 (96) 129 / 84, 2048x1152x384 (144) 43 / 35, 1536x1536x4096
-// (144) 328 / 343, 2048x1536x384 (192) 44 / 44, 2048x2048x2048 (256) 170 / 288.  The two
-// kernels add a product's K terms in different orders.
+// (144) 328 / 343, 2048x1536x384 (192) 44 / 44, 2048x2048x2048 (256) 170 / 288.  In NT
+// and NN both kernels add the K terms in the same order: an item's rows must not change with
+// what shares its micro-batch.
 constexpr int64_t F32_SMALL_TILES = 128;
 bool f32_small_tiles(int64_t M, int64_t N, int64_t splits) {
   return (M + BM - 1) / BM * ((N + BN - 1) / BN) * splits <= F32_SMALL_TILES;

@@ -548,3 +548,33 @@ def test_patch_rows_at_any_alignment(tpatch):
     torch.cuda.synchronize()
     assert torch.isfinite(outs[0][1]).all() and outs[0][1].any()
     assert all(torch.equal(a, b) for a, b in zip(*outs))
+
+
+def test_fp32_items_keep_their_bits():
+    """An fp32 item's merged rows and patch gradient do not depend on what shares its
+    micro-batch: 14 images and a clip in one call, and items of it alone, bit for bit.  Of the
+    products of the 8,920-row call (384 wide) all of the forward's run the 128x128 kernel (more
+    than 128 tiles: 70 row tiles x 3 to 12 columns, the merger 18 x 8 and 12), the small
+    groups' the 32x32 one.  The first item also against the oracle."""
+    cfg = W.EncoderConfig(hidden=384, layers=1, heads=6, mlp=1536, llm_hidden=1024,
+                          dtype="f32")
+    W.custom_spec("small_fp32", cfg)
+    grid = np.array([[1, 26, 28]] * 11 + [[2, 14, 16], [1, 20, 22], [1, 4, 6]], np.int32)
+    wl = W.make_workload("small_fp32", 0, grid_thw=grid)
+    w, X, cu = wl.weights(), wl.patches(), np.asarray(wl.cu_seqlens)
+    dM = np.random.default_rng(4).standard_normal((wl.n_merged, 1024)).astype(np.float32)
+    mo = np.concatenate([[0], np.cumsum(wl.merged_per_item)])
+    announce(f"fp32 items alone and together N={wl.n_patches}")
+    full = GpuRun(cfg, w, X, cu, grid).run(True, d_merged=dM, want_dx=True)
+    merged, dx = host(full["merged"]), host(full["dx"])
+    assert np.isfinite(merged).all() and np.isfinite(dx).all()
+    for a, b in ((0, 1), (9, 11), (11, 14)):
+        announce(f"fp32 items {a} .. {b - 1} alone")
+        rows, mrows = slice(int(cu[a]), int(cu[b])), slice(int(mo[a]), int(mo[b]))
+        one = GpuRun(cfg, w, X[rows], cu[a:b + 1] - cu[a], grid[a:b]).run(
+            True, d_merged=dM[mrows], want_dx=True)
+        assert np.array_equal(host(one["merged"]), merged[mrows]), (a, b)
+        assert np.array_equal(host(one["dx"]), dx[rows]), (a, b)
+    _, rM, _, rdx = oracle.encoder(cfg, w, X[:728], [0, 728], grid[:1], True, d_merged=dM[:182],
+                                   want_d_patches=True)
+    assert max_rel(merged[:182], rM) < TOL["f32"] and max_rel(dx[:728], rdx) < TOL["f32"]

@@ -469,3 +469,27 @@ def test_attention_f32_scores_of_minus_infinity():
     errs = [max_rel(host(o), ro), max_rel(host(lse), rlse.T), max_rel(got[:, :h], ref[0]),
             max_rel(got[:, h + rest], ref[1][:, rest]), max_rel(got[:, 2 * h:], ref[2])]
     assert max(errs) < 1e-5, errs
+
+
+@pytest.mark.parametrize("layout", [NT, NN])
+@pytest.mark.parametrize("N,K", [(1280, 1000), (392, 68), (388, 20)])
+def test_gemm_f32_rows_of_a_taller_product(layout, N, K):
+    """6,000 rows run the 128x128 kernel, 1,400 and 200 of them the 32x32 one (up to 128 tiles
+    of 128x128); both add K in the same order, so the rows are the same bits: with K of whole
+    and ragged quarters of 16-deep steps, and of fewer steps than quarters."""
+    import paper_2607_03229_amd as mp
+    torch, dev = torch_dev()
+    rng, M = np.random.default_rng(K), 6000
+    announce(f"gemm f32 rows of a taller product layout={layout} N={N} K={K}")
+    A, B = rnd(rng, (M, K), "f32"), rnd(rng, (N, K) if layout == NT else (K, N), "f32")
+    dA, dB, bias = to_dev(A, "f32"), to_dev(B, "f32"), to_dev(rnd(rng, (N,), "f32"), "f32")
+    for epi in (E_F32, E_GELU):
+        out = []
+        for rows in (M, 1400, 200):
+            C = nans((rows, N), "f32")
+            mp.op_gemm(0, layout, epi, rows, N, K, dA, K, dB, dB.shape[1], C, N,
+                       bias=None if epi == E_F32 else bias)
+            out.append(C)
+        if epi == E_F32:
+            assert max_rel(host(out[0]), _ref_product(layout, A, B)) < 2e-5
+        assert all(torch.equal(out[0][:c.shape[0]], c) for c in out[1:]), epi
