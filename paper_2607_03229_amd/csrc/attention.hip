@@ -829,9 +829,10 @@ __global__ __launch_bounds__(256) void attn_fwd_f32_kernel(AttnArgs p) {
   constexpr int ND = D / 16;
   __shared__ f32x4 red[3 * ND][64];
   __shared__ float2 ml[4][64];
-  const int sub = blockIdx.x % F32_SUB, wh = blockIdx.x / F32_SUB;
-  const int4 wk = p.work[wh / p.heads];
-  const int head = wh % p.heads;
+  const int sub = blockIdx.x % F32_SUB;
+  const uint32_t pair = p.pair0 + blockIdx.x / F32_SUB;
+  const int4 wk = p.work[pair / (uint32_t)p.heads];
+  const int head = (int)(pair % (uint32_t)p.heads);
   const int q0 = wk.x + 16 * sub, s0 = wk.y, last = wk.z - 1;
   if (q0 > last) return;
   const int w = threadIdx.x >> 6, l = threadIdx.x & 63, g = l >> 4, r = l & 15;
@@ -909,9 +910,10 @@ template <int D>
 __global__ __launch_bounds__(256) void attn_bwd_dq_f32_kernel(AttnArgs p) {
   constexpr int ND = D / 16;
   __shared__ f32x4 red[3 * ND][64];
-  const int sub = blockIdx.x % F32_SUB, wh = blockIdx.x / F32_SUB;
-  const int4 wk = p.work[wh / p.heads];
-  const int head = wh % p.heads;
+  const int sub = blockIdx.x % F32_SUB;
+  const uint32_t pair = p.pair0 + blockIdx.x / F32_SUB;
+  const int4 wk = p.work[pair / (uint32_t)p.heads];
+  const int head = (int)(pair % (uint32_t)p.heads);
   const int q0 = wk.x + 16 * sub, s0 = wk.y, last = wk.z - 1;
   if (q0 > last) return;
   const int w = threadIdx.x >> 6, l = threadIdx.x & 63, g = l >> 4, r = l & 15;
@@ -978,9 +980,10 @@ template <int D>
 __global__ __launch_bounds__(256) void attn_bwd_dkdv_f32_kernel(AttnArgs p) {
   constexpr int ND = D / 16;
   __shared__ f32x4 red[3 * ND][64];
-  const int sub = blockIdx.x % F32_SUB, wh = blockIdx.x / F32_SUB;
-  const int4 wk = p.work[wh / p.heads];
-  const int head = wh % p.heads;
+  const int sub = blockIdx.x % F32_SUB;
+  const uint32_t pair = p.pair0 + blockIdx.x / F32_SUB;
+  const int4 wk = p.work[pair / (uint32_t)p.heads];
+  const int head = (int)(pair % (uint32_t)p.heads);
   const int key0 = wk.x + 16 * sub, s0 = wk.y, last = wk.z - 1;
   if (key0 > last) return;
   const int w = threadIdx.x >> 6, l = threadIdx.x & 63, g = l >> 4, r = l & 15;
@@ -1089,20 +1092,35 @@ hipError_t dkdv_bf16(const AttnArgs& a, hipStream_t s) {
     hipLaunchKernelGGL((attn_bwd_dkdv_kernel<D, 2>), dim3(a.n_work * a.heads), dim3(64 * NW), 0, s, a);
   return hipGetLastError();
 }
+// fp32: eight blocks of 256 threads per (work item, head) pair, launched 2^20 pairs at a time,
+// since one launch is limited to 2^32 threads (one-row segments reach that at 131,073 rows of
+// 16 heads).
+constexpr int64_t F32_PAIRS = 1 << 20;
+template <class Kernel>
+hipError_t launch_f32(Kernel kernel, const AttnArgs& a0, hipStream_t s) {
+  AttnArgs a = a0;
+  const int64_t pairs = (int64_t)a.n_work * a.heads;
+  if (pairs > INT32_MAX) return hipErrorInvalidConfiguration;
+  for (int64_t p0 = 0; p0 < pairs; p0 += F32_PAIRS) {
+    a.pair0 = (uint32_t)p0;
+    const int64_t n = pairs - p0 < F32_PAIRS ? pairs - p0 : F32_PAIRS;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(n * F32_SUB)), dim3(256), 0, s, a);
+    const hipError_t r = hipGetLastError();
+    if (r != hipSuccess) return r;
+  }
+  return hipSuccess;
+}
 template <int D>
 hipError_t fwd_f32(const AttnArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL(attn_fwd_f32_kernel<D>, dim3(a.n_work * a.heads * F32_SUB), dim3(256), 0, s, a);
-  return hipGetLastError();
+  return launch_f32(attn_fwd_f32_kernel<D>, a, s);
 }
 template <int D>
 hipError_t dq_f32(const AttnArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL(attn_bwd_dq_f32_kernel<D>, dim3(a.n_work * a.heads * F32_SUB), dim3(256), 0, s, a);
-  return hipGetLastError();
+  return launch_f32(attn_bwd_dq_f32_kernel<D>, a, s);
 }
 template <int D>
 hipError_t dkdv_f32(const AttnArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL(attn_bwd_dkdv_f32_kernel<D>, dim3(a.n_work * a.heads * F32_SUB), dim3(256), 0, s, a);
-  return hipGetLastError();
+  return launch_f32(attn_bwd_dkdv_f32_kernel<D>, a, s);
 }
 
 }  // namespace
