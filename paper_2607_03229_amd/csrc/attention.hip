@@ -734,6 +734,21 @@ __global__ __launch_bounds__(64 * NW, NS == 2 ? 3 : 2) void attn_bwd_dq_kernel(A
 // side stream's weight gradients), 34.
 constexpr int F32_SUB = ATTN_TILE / 16;   // 16-row sub-tiles of a work item
 
+// The tensors may start at any float (rows are whole multiples of 32 floats apart): accesses
+// are declared 4-byte aligned, which the global loads and stores of this width allow.
+typedef __attribute__((ext_vector_type(4), aligned(4))) float f32x4_any;
+typedef __attribute__((ext_vector_type(2), aligned(4))) float f32x2_any;
+__device__ __forceinline__ float4 load4(const float* p) {
+  const f32x4_any x = *reinterpret_cast<const f32x4_any*>(p);
+  return make_float4(x[0], x[1], x[2], x[3]);
+}
+__device__ __forceinline__ void store4(float* p, float a, float b, float c, float d) {
+  *reinterpret_cast<f32x4_any*>(p) = f32x4_any{a, b, c, d};
+}
+__device__ __forceinline__ void store2(float* p, float a, float b) {
+  *reinterpret_cast<f32x2_any*>(p) = f32x2_any{a, b};
+}
+
 // Row form of rows r0.. (clamped to `last`): piece f at X[row][16f + 4g].
 template <int D> struct RowsF32 {
   float4 v[D / 16];
@@ -743,7 +758,7 @@ __device__ __forceinline__ void load_rows(RowsF32<D>& R, const float* X, int64_t
                                           int last, int g) {
   const float* p = X + (int64_t)min(row, last) * ld + 4 * g;
 #pragma unroll
-  for (int f = 0; f < D / 16; ++f) R.v[f] = *reinterpret_cast<const float4*>(p + 16 * f);
+  for (int f = 0; f < D / 16; ++f) R.v[f] = load4(p + 16 * f);
 }
 // Transposed form of rows r0 + 4g + s; rows past `last` are zero.
 template <int D> struct ColsF32 {
@@ -814,10 +829,10 @@ __device__ __forceinline__ void store_grad_f32(const AttnArgs& p, float* out, in
       const int j = 8 * dt + 2 * g;
       rope_unrotate(x[0], x[1], rope_cs(p.rope_pos, p.rope_tab, D, row, j));
       rope_unrotate(x[2], x[3], rope_cs(p.rope_pos, p.rope_tab, D, row, j + 1));
-      *reinterpret_cast<float2*>(out + j) = make_float2(x[0], x[2]);
-      *reinterpret_cast<float2*>(out + j + D / 2) = make_float2(x[1], x[3]);
+      store2(out + j, x[0], x[2]);
+      store2(out + j + D / 2, x[1], x[3]);
     } else {
-      *reinterpret_cast<float4*>(out + 16 * dt + 4 * g) = make_float4(x[0], x[1], x[2], x[3]);
+      store4(out + 16 * dt + 4 * g, x[0], x[1], x[2], x[3]);
     }
   }
 }
@@ -900,8 +915,7 @@ __global__ __launch_bounds__(256) void attn_fwd_f32_kernel(AttnArgs p) {
   float* O = reinterpret_cast<float*>(p.out) + head * D + (int64_t)row * p.ldo;
 #pragma unroll
   for (int dt = 0; dt < ND; ++dt)
-    *reinterpret_cast<float4*>(O + 16 * dt + 4 * g) =
-        make_float4(o[dt][0] / tot, o[dt][1] / tot, o[dt][2] / tot, o[dt][3] / tot);
+    store4(O + 16 * dt + 4 * g, o[dt][0] / tot, o[dt][1] / tot, o[dt][2] / tot, o[dt][3] / tot);
   if (g == 0 && p.lse) p.lse[(int64_t)head * p.N + row] = M + logf(tot);
 }
 
@@ -1054,8 +1068,7 @@ __global__ __launch_bounds__(256) void attn_bwd_dkdv_f32_kernel(AttnArgs p) {
   float* dV = reinterpret_cast<float*>(p.dv) + head * D + (int64_t)row * p.ldd;
 #pragma unroll
   for (int dt = 0; dt < ND; ++dt)
-    *reinterpret_cast<float4*>(dV + 16 * dt + 4 * g) =
-        make_float4(dv[dt][0], dv[dt][1], dv[dt][2], dv[dt][3]);
+    store4(dV + 16 * dt + 4 * g, dv[dt][0], dv[dt][1], dv[dt][2], dv[dt][3]);
   store_grad_f32<D>(p, reinterpret_cast<float*>(p.dk) + head * D + (int64_t)row * p.ldd, row, g,
                     dk);
 }

@@ -517,3 +517,31 @@ def test_attention_f32_more_pairs_than_one_launch():
     assert torch.equal(o, qkv[:, 2 * h:])
     assert (dqkv[:, 2 * h:] - dO).abs().max() < 1e-4
     assert dqkv[:, :2 * h].abs().max() < 1e-4
+
+
+@pytest.mark.parametrize("d", [32, 80])
+def test_attention_f32_at_any_float(d):
+    """The fp32 attention takes tensors that start at any float: the same bits as for tensors
+    on 16 bytes."""
+    import paper_2607_03229_amd as mp
+    torch, dev = torch_dev()
+    lens, heads = [65, 17, 145], 2
+    N, h = sum(lens), heads * d
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    announce(f"fp32 attention d={d} on tensors one to three floats off 16 bytes")
+    gen = torch.Generator(device=dev).manual_seed(d)
+    qkv, dO = (torch.randn((N, n), device=dev, generator=gen) for n in (3 * h, h))
+    scratch = torch.empty(mp.op_scratch_bytes(N, heads, h, 3), dtype=torch.uint8, device=dev)
+    outs = []
+    for off in range(4):
+        def at(t):
+            out = torch.full((t.numel() + 4,), float("nan"), device=dev)[off:off + t.numel()]
+            return out.view(t.shape).copy_(t)
+        tq, tdo, o, dqkv = at(qkv), at(dO), at(torch.empty_like(dO)), at(torch.empty_like(qkv))
+        lse = nans((heads, N), "f32")
+        mp.op_attention_fwd(0, tq, N, heads, d, cu, o, lse, scratch)
+        mp.op_attention_bwd(0, tq, o, tdo, lse, N, heads, d, cu, dqkv, scratch)
+        outs.append((o, lse, dqkv))
+    torch.cuda.synchronize()
+    assert torch.isfinite(outs[0][2]).all()
+    assert all(torch.equal(a, b) for out in outs[1:] for a, b in zip(outs[0], out))
