@@ -346,6 +346,7 @@ struct FwdWeight {
   const void* W;
   int64_t out, in, ld;
   bool perm = false;
+  bool direct = true;        // may be read as it lies
   int tile = -1;             // gemm_direct_tile, or -1: transposed
   const void* wt = nullptr;  // the transposed copy
 };
@@ -357,7 +358,7 @@ mpipe_status prepare_weights(Ctx& x, FwdWeight* fw, int n, int64_t M) {
   char* dst = x.ws + x.P.ws_wt;
   for (int i = 0; i < n; ++i) {
     FwdWeight& f = fw[i];
-    f.tile = gemm_direct_tile(x.dt, M, f.out, f.in, f.W, f.ld);
+    f.tile = f.direct ? gemm_direct_tile(x.dt, M, f.out, f.in, f.W, f.ld) : -1;
     if (f.tile >= 0) continue;
     TJob& j = jobs[nj++];
     j.src = f.W;
@@ -445,6 +446,9 @@ mpipe_status forward(Ctx& x, const void* patches, void* merged, char* tape) {
                        {x.W(blk_param(c, l, B_PROJW)), h, h, h},
                        {x.W(blk_param(c, l, B_FC1W)), m, h, h},
                        {x.W(blk_param(c, l, B_FC2W)), h, m, m}};
+    // Weight rows in interleaved order are read by the kernels that want their operands on 16
+    // bytes (bf16) or take any (fp32); a bf16 buffer elsewhere gets the reordered copy.
+    fw[0].direct = x.dt != DT_BF16 || (reinterpret_cast<uintptr_t>(base) & 15) == 0;
     MP_RET(prepare_weights(x, fw, 4, N));
     MP_CHECK(run(x.e, x.s, "layernorm", 0, [&] {
       return layernorm_fwd(x.dt, hin, h, N, (int)h, x.W(blk_param(c, l, B_LN1G)),

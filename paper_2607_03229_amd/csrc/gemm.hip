@@ -36,9 +36,9 @@ struct Regs4 { uint4 v[4]; };
 
 // K-contiguous operand X[rows][ld]: tile rows r0..r0+127, k in [k0, k0+BK).
 // Thread t loads chunk (t & 7) of rows (t >> 3) + 32 i.
-template <class T, class RowOf>
+template <class T>
 __device__ __forceinline__ void load_kcontig(Regs4& R, const T* X, int64_t ld, int rows, int r0,
-                                             int k0, int kend, RowOf row_of) {
+                                             int k0, int kend) {
   constexpr int VEC = KStep<T>::VEC;
   const int t = threadIdx.x;
   const int c = t & 7;
@@ -46,7 +46,7 @@ __device__ __forceinline__ void load_kcontig(Regs4& R, const T* X, int64_t ld, i
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     int row = r0 + (t >> 3) + 32 * i;
-    row = row_of(row < rows ? row : rows - 1);
+    row = row < rows ? row : rows - 1;
     if (k < kend)
       R.v[i] = *reinterpret_cast<const uint4*>(X + (int64_t)row * ld + k);
     else
@@ -292,16 +292,12 @@ __global__ __launch_bounds__(NTHR, 2) void gemm_kernel(GemmArgs p) {
   [[maybe_unused]] int left = quarter;
   if constexpr (QUARTERS) clear(total);
 
-  // B's row behind output column n (GemmArgs::rope_rows)
-  auto weight_row = [&](int n) {
-    return EPI == EPI_STORE_ROPE && p.rope_rows ? rope_weight_row(n, p.rope_d, p.rope_cols) : n;
-  };
   Regs4 ra, rb;
   auto gload = [&](int k0) {
     if constexpr (AK) load_kmajor<T>(ra, A, p.lda, p.M, m0, k0, kend);
-    else load_kcontig<T>(ra, A, p.lda, p.M, m0, k0, kend, [](int row) { return row; });
+    else load_kcontig<T>(ra, A, p.lda, p.M, m0, k0, kend);
     if constexpr (BKM) load_kmajor<T>(rb, B, p.ldb, p.N, n0, k0, kend);
-    else load_kcontig<T>(rb, B, p.ldb, p.N, n0, k0, kend, weight_row);
+    else load_kcontig<T>(rb, B, p.ldb, p.N, n0, k0, kend);
   };
   auto lstore = [&](int buf) {
     if constexpr (AK) store_kmajor<T>(lds_a[buf], ra);
@@ -449,6 +445,9 @@ hipError_t gemm(int dtype, int layout, int epi, const GemmArgs& a, hipStream_t s
     if (t != TILE_BIG) return gemm_small(layout, epi, t, a, s);
     if (a.M >= 512 && a.N >= 256) return gemm_big(layout, epi, a, s);
   }
+  if (dtype == DT_F32 && f32_small_tiles(a.M, a.N, a.kps > 0 ? (a.K + a.kps - 1) / a.kps : 1))
+    return gemm_f32_small(layout, epi, a, s);
+  if (a.rope_rows) return hipErrorInvalidValue;   // the general kernel takes B as it lies
   if (dtype == DT_BF16) {
     switch (layout) {
       case GEMM_NT: return dispatch_epi<bf16, false, false>(a, epi, s);
@@ -456,8 +455,6 @@ hipError_t gemm(int dtype, int layout, int epi, const GemmArgs& a, hipStream_t s
       case GEMM_TN: return dispatch_epi<bf16, true, true>(a, epi, s);
     }
   } else {
-    if (f32_small_tiles(a.M, a.N, a.kps > 0 ? (a.K + a.kps - 1) / a.kps : 1))
-      return gemm_f32_small(layout, epi, a, s);
     switch (layout) {
       case GEMM_NT: return dispatch_epi<float, false, false>(a, epi, s);
       case GEMM_NN: return dispatch_epi<float, false, true>(a, epi, s);
