@@ -37,6 +37,13 @@ mpipe_status mpipe_op_gemm(int32_t dtype, int32_t layout, int32_t epilogue, int3
                            void* C2, int64_t ldc2, int32_t beta, int32_t k_per_split,
                            int64_t split_stride, void* hip_stream);
 
+/* The kernel mpipe_op_gemm runs a product on (host query, no device work), for dense
+ * operands on 16 bytes: 0 general 128x128, 1 fp32 32x32 tiles, 2 / 3 / 4 bf16 tiles of
+ * 64x64 / 64x128 / 128x128, 5 the large bf16 tiles (128x256 for NN, 256x256 for NT and
+ * TN).  -1 for arguments out of range. */
+int32_t mpipe_op_gemm_kernel(int32_t dtype, int32_t layout, int32_t epilogue, int32_t M,
+                             int32_t N, int32_t K, int32_t k_per_split);
+
 /* Deterministic split-K reduction of the weight gradient (the Accumulate edge of
  * Sec. 4.1: gradients are added into what the buffer holds):
  *   out[m][n] += sum over s = 0 .. splits-1, in that order, of part[s][m][n]

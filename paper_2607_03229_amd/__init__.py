@@ -10,7 +10,7 @@ from ._binding import (  # noqa: F401
     merge_scatter, merge_gather, merge_check_indices, merge_check_indices_noalloc,
     CHECK_NOALLOC_MAX_ROWS,
     op_gemm, op_layernorm_fwd, op_layernorm_bwd, op_rope, op_attention_fwd,
-    op_attention_bwd, op_scratch_bytes, op_splitk_reduce, gemm_split,
+    op_attention_bwd, op_scratch_bytes, op_splitk_reduce, gemm_split, gemm_kernel,
     F32, BF16, OK, NOOP_FROZEN,
     owner_map, OWNER_GREEDY, OWNER_EXACT, OWNER_REFINED,
     schedule_valid, Derived, EVENT_FIELDS,

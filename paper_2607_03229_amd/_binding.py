@@ -77,6 +77,7 @@ def load():
         "mpipe_profile_read": (i32, [P, P, i32, P, i32, P, P, P]),
         "mpipe_op_gemm": (st, [i32, i32, i32, i32, i32, i32, P, i64, P, i64, P, i64, P, P, i64,
                                P, i64, i32, i32, i64, P]),
+        "mpipe_op_gemm_kernel": (i32, [i32] * 7),
         "mpipe_op_splitk_reduce": (st, [P, i32, i64, i64, P, i64, P]),
         "mpipe_op_weight_grad_splits": (i32, [i64, i64, i64]),
         "mpipe_op_layernorm_fwd": (st, [i32, P, i64, i32, P, P, C.c_float, P, P, P, P]),
@@ -465,6 +466,18 @@ def op_gemm(dtype: int, layout: int, epilogue: int, M: int, N: int, K: int, A, l
     _check(load().mpipe_op_gemm(dtype, layout, epilogue, M, N, K, _ptr(A), lda, _ptr(B), ldb,
                                 _ptr(Cout), ldc, _ptr(bias), _ptr(aux), ld_aux, _ptr(C2), ldc2,
                                 beta, k_per_split, split_stride, _stream(stream)))
+
+
+GEMM_KERNELS = ("general", "f32_32x32", "64x64", "64x128", "128x128", "large")
+
+
+def gemm_kernel(dtype: int, layout: int, epilogue: int, M: int, N: int, K: int,
+                k_per_split: int = 0) -> str:
+    """The kernel op_gemm runs a product of dense, 16-byte aligned operands on."""
+    k = int(load().mpipe_op_gemm_kernel(dtype, layout, epilogue, M, N, K, k_per_split))
+    if k < 0:
+        raise MpipeError(-1, "gemm_kernel: argument out of range")
+    return GEMM_KERNELS[k]
 
 
 def op_splitk_reduce(part, splits: int, M: int, N: int, out, ldo: int, stream=None) -> None:

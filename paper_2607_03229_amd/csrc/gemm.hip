@@ -15,6 +15,7 @@
 // (64 KB); the next tile's global loads are in flight during the MFMAs.
 // Blocks are remapped so that consecutive tiles land on the same XCD and walk
 // the output in groups of 8 tile-rows (L2 reuse of A rows and B columns).
+#include <algorithm>
 #include <type_traits>
 
 #include "common.h"
@@ -409,18 +410,29 @@ bool f32_small_tiles(int64_t M, int64_t N, int64_t splits) {
 }  // namespace
 
 namespace {
+int splits_of(const GemmArgs& a) { return a.kps > 0 ? std::max(1, (a.K + a.kps - 1) / a.kps) : 1; }
 // The tile gemm() runs a takes_tiled problem on.  (gemm_small.hip has the weight-gradient
 // layout with the fp32 epilogue only.)
 int tile_of(int layout, int epi, const GemmArgs& a) {
   if (a.tile >= 0) return a.tile;
   if (layout == GEMM_TN && epi != EPI_F32) return TILE_BIG;
-  return choose_tile(layout, a.M, a.N, a.K, a.kps > 0 ? (a.K + a.kps - 1) / a.kps : 1);
+  return choose_tile(layout, a.M, a.N, a.K, splits_of(a));
 }
 }  // namespace
 
+int gemm_kernel_of(int dtype, int layout, int epi, const GemmArgs& a) {
+  if (takes_tiled(dtype, epi, a)) {
+    const int t = tile_of(layout, epi, a);
+    if (t != TILE_BIG) return GEMM_K_TILES + t;
+    if (a.M >= 512 && a.N >= 256) return GEMM_K_TILES + TILE_BIG;
+  }
+  if (dtype == DT_F32 && f32_small_tiles(a.M, a.N, splits_of(a))) return GEMM_K_F32_SMALL;
+  return GEMM_K_GENERAL;
+}
+
 bool gemm_fused_colsum(int dtype, int layout, int epi, const GemmArgs& a) {
-  return layout == GEMM_NN && epi == EPI_GELU_BWD && a.kps <= 0 && takes_tiled(dtype, epi, a) &&
-         tile_of(layout, epi, a) == TILE_BIG;
+  return layout == GEMM_NN && epi == EPI_GELU_BWD && a.kps <= 0 &&
+         gemm_kernel_of(dtype, layout, epi, a) == GEMM_K_TILES + TILE_BIG;
 }
 
 int gemm_direct_tile(int dtype, int64_t M, int64_t N, int64_t K, const void* W, int64_t ldw) {
@@ -440,13 +452,10 @@ hipError_t gemm(int dtype, int layout, int epi, const GemmArgs& a, hipStream_t s
   if (a.colsum && !gemm_fused_colsum(dtype, layout, epi, a)) return hipErrorInvalidValue;
   if (a.rope_rows && (layout != GEMM_NT || epi != EPI_STORE_ROPE || a.tile < 0))
     return hipErrorInvalidValue;
-  if (takes_tiled(dtype, epi, a)) {
-    const int t = tile_of(layout, epi, a);
-    if (t != TILE_BIG) return gemm_small(layout, epi, t, a, s);
-    if (a.M >= 512 && a.N >= 256) return gemm_big(layout, epi, a, s);
-  }
-  if (dtype == DT_F32 && f32_small_tiles(a.M, a.N, a.kps > 0 ? (a.K + a.kps - 1) / a.kps : 1))
-    return gemm_f32_small(layout, epi, a, s);
+  const int kernel = gemm_kernel_of(dtype, layout, epi, a);
+  if (kernel == GEMM_K_TILES + TILE_BIG) return gemm_big(layout, epi, a, s);
+  if (kernel >= GEMM_K_TILES) return gemm_small(layout, epi, kernel - GEMM_K_TILES, a, s);
+  if (kernel == GEMM_K_F32_SMALL) return gemm_f32_small(layout, epi, a, s);
   if (a.rope_rows) return hipErrorInvalidValue;   // the general kernel takes B as it lies
   if (dtype == DT_BF16) {
     switch (layout) {

@@ -50,6 +50,10 @@ struct GemmArgs {
   int tile = -1;   // bf16: kernel tile (TILE_*, plan.h) chosen by the caller; -1: by size
 };
 hipError_t gemm(int dtype, int layout, int epi, const GemmArgs& a, hipStream_t s);
+// The kernel gemm() runs a problem on: the general one (gemm.hip), the fp32 32x32 one
+// (gemm_f32.hip), or GEMM_K_TILES + a bf16 tile (TILE_*, plan.h).
+enum { GEMM_K_GENERAL, GEMM_K_F32_SMALL, GEMM_K_TILES };
+int gemm_kernel_of(int dtype, int layout, int epi, const GemmArgs& a);
 // A Linear's forward product Y[M][N] = X W^T from the weight as stored, W [N][K] (row stride
 // ldw): the tile to pass as GemmArgs::tile with layout NT, or -1 where transposing W and
 // multiplying in layout NN is faster (or W is not aligned for direct reads).

@@ -93,6 +93,21 @@ mpipe_status mpipe_op_gemm(int32_t dtype, int32_t layout, int32_t epi, int32_t M
   return MPIPE_OK;
 }
 
+int32_t mpipe_op_gemm_kernel(int32_t dtype, int32_t layout, int32_t epi, int32_t M, int32_t N,
+                             int32_t K, int32_t kps) {
+  if (dtype < 0 || dtype > 1 || layout < 0 || layout > 2 || epi < 0 || epi > 4 || M < 0 || N < 0 ||
+      K < 0)
+    return -1;
+  const int vec = dtype == 1 ? 8 : 4;
+  GemmArgs a;   // null pointers: on any alignment
+  a.lda = layout == GEMM_TN ? M : K;
+  a.ldb = layout == GEMM_NT ? K : ((int64_t)N + vec - 1) / vec * vec;
+  a.ldc = a.ld_aux = a.ldc2 = N;
+  a.split_stride = (int64_t)M * N;
+  a.M = M; a.N = N; a.K = K; a.kps = kps;
+  return gemm_kernel_of(dtype, layout, epi, a);
+}
+
 mpipe_status mpipe_op_splitk_reduce(const float* part, int32_t splits, int64_t M, int64_t N,
                                     float* out, int64_t ldo, void* stream) {
   if (splits < 1 || M < 0 || N < 0 || ldo < N)

@@ -215,3 +215,23 @@ def test_merger_only_mode_host_side(L):
                              fake, fake, fake, fake, part["workspace"], None)
     assert rc == -1 and "d_patches" in B.last_error()
     enc.close()
+
+
+def test_gemm_kernel_query(L):
+    """The kernel of a product (host query): misaligned column counts and fp32 past 128 tiles
+    of 128x128 go to the general kernel, few fp32 tiles to the 32x32 one, a bf16 product with
+    a large tile for each CU to the large ones; an empty K splits no further than a short one."""
+    import paper_2607_03229_amd as mp
+    NT, NN, TN = 0, 1, 2
+    assert mp.gemm_kernel(1, NT, 0, 300, 300, 64) == "general"
+    assert mp.gemm_kernel(0, NN, 0, 1408, 1408, 64) == "f32_32x32"        # 121 tiles
+    assert mp.gemm_kernel(0, NN, 0, 1408, 1536, 64) == "general"          # 132 tiles
+    assert mp.gemm_kernel(0, TN, 4, 700, 700, 1000, 256) == "general"     # 36 tiles, 4 splits
+    assert mp.gemm_kernel(0, TN, 4, 700, 700, 1000, 512) == "f32_32x32"
+    assert mp.gemm_kernel(0, TN, 4, 2048, 2048, 0, 64) == "general"
+    assert mp.gemm_kernel(1, NT, 4, 300, 64, 64) == "64x64"
+    for layout, M in ((NN, 128 * 129), (NT, 256 * 129)):                  # 258 tiles
+        assert mp.gemm_kernel(1, layout, 0, M, 512, 128) == "large"
+    assert mp.gemm_kernel(1, NN, 0, 128 * 129, 248, 128) != "large"       # N < 256
+    with pytest.raises(mp.MpipeError):
+        mp.gemm_kernel(1, 3, 0, 8, 8, 8)
