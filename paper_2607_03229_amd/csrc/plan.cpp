@@ -103,38 +103,54 @@ std::vector<float> rope_table(const Cfg& c, int positions) {
 // side stream, 304.3 -> 293.5 ms/step without it.
 constexpr int64_t kMaxSplitK = 4;
 
-// Rounds of 256 CUs times a block's time: its 64-deep K steps and its epilogue, each
-// measured on MI355X at one block per CU.  ns per step by tile (NT and NN / TN): 64x64
-// 180 / 228, 64x128 330 / 357, 128x128 480 / 521, large 700 / 1000; the epilogue moves 4
-// bytes per element (8 for TN, which adds into its output) at 20 bytes per ns; small tiles
-// lose another 15 % once they share the chip's memory paths over several rounds.  Against
-// measured products (us, expected / measured): NT 2700x1280x1280 128x128 12.9 / 15.9, large
-// 20.5 / 20.8; 1408x5120x1280 128x128 29.7 / 29.5, large 20.5 / 23.3; 256x1280x5120 64x64
-// 15.2 / 18.5, 64x128 28.0 / 29.0.
-// The large kernels need M >= 512 and N >= 256, and keep every product that gives each CU a
-// tile (10528x1024x1024: 332 large tiles, 65 us in the forward; 128x128 tiles took 70).  A
-// weight gradient runs beside the caller's stream, where CU time is what counts: it leaves
-// the large tile only where at most 64 CUs would have one (1280x1280x1408: 25 large tiles,
-// 43 us in the step, 17 with 64x128; 75 or 100 large tiles took as long as 128x128 ones).
+// A product's expected time on each tile: rounds of the chip's slots, each of the K steps that
+// a block walks (64 deep) and a fixed part (ring fill and epilogue; `once` is what of the first
+// round hides behind the launch).  64x64 tiles and the large NN ones run two blocks to a CU,
+// which share its memory paths: a round of up to 256 blocks has its own figures.  Fitted to
+// some 1,500 products measured on MI355X with weights that come from HBM (M 16 to 7,664,
+// N and K 128 to 5,120; rms error 8 to 10 %): over them the tile taken is 0.3 % (NT), 0.1 %
+// (NN) slower than the fastest on average, 11 % at most, and never slower than the large one.
+// Examples (us, 64x64 / 64x128 / 128x128 / large): NT 308x1280x5120 19 / 29 / 41 / -,
+// 2856x2048x512 16 / 22 / 17 / 20, NN 2232x1280x1280 16 / 22 / 16 / 20.
+struct TileTime {
+  double step, fixed;     // of a full round
+  double step1, fixed1;   // of a round of up to 256 blocks, where a round is 512
+  double once;
+};
+const TileTime kTileTime[3][4] = {
+    {{380, 1100, 190, 1000, 0}, {305, 4600, 0, 0, -2000}, {467, 5200, 0, 0, -2700},
+     {1200, 10000, 0, 0, -3000}},                                                        // NT
+    {{380, 1100, 190, 1000, 0}, {305, 4600, 0, 0, -2000}, {467, 5200, 0, 0, -2700},
+     {1440, 9600, 630, 7100, -2000}},                                                    // NN
+    {{344, 3000, 134, 2400, 0}, {361, 4500, 0, 0, -1500}, {550, 7400, 0, 0, -3100},
+     {1050, 16000, 0, 0, -3100}},                                                        // TN
+};
+
+// The large kernels need M >= 512 and N >= 256; they keep every product that gives each CU a
+// tile, and those where the model is within 5 %.  A weight gradient runs beside the caller's
+// stream, where CU time is what counts: it leaves the large tile only where at most 64 CUs
+// would have one (1280x1280x1408: 25 large tiles, 43 us in the step, 17 with 64x128; 75 or 100
+// large tiles took as long as 128x128 ones).
 int choose_tile(int layout, int64_t M, int64_t N, int64_t K, int64_t splits,
                 double big_extra_ns) {
   const bool tn = layout == 2, nn = layout == 1;
   const int bm[4] = {64, 64, 128, nn ? 128 : 256}, bn[4] = {64, 128, 128, 256};
-  const double step[4] = {tn ? 228. : 180., tn ? 357. : 330., tn ? 521. : 480.,
-                          nn ? 700. : 1000.};
   auto blocks = [&](int t) { return (M + bm[t] - 1) / bm[t] * ((N + bn[t] - 1) / bn[t]); };
   const bool big = M >= 512 && N >= 256;
   if (big && (tn ? splits > 1 || blocks(TILE_BIG) > 64 : blocks(TILE_BIG) * splits > 256))
     return TILE_BIG;
+  const double steps = (double)((K + 64 * splits - 1) / (64 * splits));
   int best = -1;
   double best_ns = 0;
   for (int t = TILE_64x64; t <= TILE_BIG; ++t) {
     if (t == TILE_BIG && !big) break;
-    const int64_t rounds = (blocks(t) * splits + 255) / 256;
-    double ns = (double)rounds * ((double)((K + 64 * splits - 1) / (64 * splits)) * step[t] +
-                                  bm[t] * bn[t] * (tn ? 8 : 4) / 20.0);
-    if (t == TILE_BIG) ns += big_extra_ns;
-    else if (rounds > 1) ns *= 1.15;
+    const TileTime& T = kTileTime[layout][t];
+    const int64_t n = blocks(t) * splits, slots = T.step1 > 0 ? 512 : 256;
+    const bool half = T.step1 > 0 && n % slots > 0 && n % slots <= 256;   // the last round
+    const int64_t rounds = (n + slots - 1) / slots - half;
+    double ns = (double)rounds * (steps * T.step + T.fixed) +
+                (half ? steps * T.step1 + T.fixed1 : 0.0) + T.once;
+    if (t == TILE_BIG) ns = 0.95 * ns + big_extra_ns;
     if (best < 0 || ns < best_ns) {
       best = t;
       best_ns = ns;

@@ -235,3 +235,30 @@ def test_gemm_kernel_query(L):
     assert mp.gemm_kernel(1, NN, 0, 128 * 129, 248, 128) != "large"       # N < 256
     with pytest.raises(mp.MpipeError):
         mp.gemm_kernel(1, 3, 0, 8, 8, 8)
+
+
+# us on MI355X of 64x64 / 64x128 / 128x128 / large tiles (weights from HBM); the large tile
+# takes M >= 512 and N >= 256 only
+MEASURED_TILES = {
+    (0, 1408, 4096, 1024): (22.5, 29.8, 24.4, 28.8), (0, 2856, 1920, 640): (18.9, 25.2, 20.2, 23.0),
+    (0, 4096, 1536, 512): (16.5, 22.3, 17.3, 20.2), (0, 5988, 1024, 1024): (23.0, 30.2, 24.8, 30.3),
+    (0, 308, 1280, 5120): (18.7, 29.0, 40.6), (0, 648, 2048, 2048): (14.1, 15.3, 19.2, 43.2),
+    (0, 7664, 3840, 1280): (126.9, 157.7, 117.5, 80.8),
+    (1, 2232, 1280, 1280): (15.6, 21.6, 16.1, 20.4), (1, 1064, 1024, 1024): (8.8, 10.9, 13.1, 17.2),
+    (1, 308, 4096, 1024): (8.9, 11.0, 12.7), (1, 3264, 1176, 1280): (22.2, 23.1, 30.8, 21.5),
+    (1, 7664, 1280, 5120): (163.7, 149.5, 134.4, 117.8),
+    (2, 1280, 1280, 700): (9.4, 11.1, 13.9, 26.7), (2, 5120, 5120, 1408): (126.8, 168.3, 131.3, 96.9),
+}
+
+
+@pytest.mark.parametrize("product", MEASURED_TILES, ids=str)
+def test_gemm_tile_is_near_the_fastest(L, product):
+    """The tile taken is within 10 % of the fastest measured one (near the model's
+    largest miss) and 5 % of the large one, at sizes on both sides of the rules."""
+    import paper_2607_03229_amd as mp
+    layout, M, N, K = product
+    us = MEASURED_TILES[product]
+    took = us[("64x64", "64x128", "128x128", "large").index(
+        mp.gemm_kernel(1, layout, 4 if layout == 2 else 0, M, N, K))]
+    assert took <= 1.1 * min(us)
+    assert len(us) < 4 or took <= 1.05 * us[3]
