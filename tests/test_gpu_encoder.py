@@ -185,9 +185,9 @@ def test_invariants_on_gpu():
 
 
 def test_side_stream_is_bitwise_neutral():
-    """The backward's weight-gradient work on the internal stream (default) gives the
-    same bits as running everything on the caller's stream, including accumulation
-    into a non-zero d_weights and the patch gradient."""
+    """The backward's weight-gradient work on the internal stream gives the same bits as
+    running everything on the caller's stream (what a micro-batch of this size does by
+    itself), including accumulation into a non-zero d_weights and the patch gradient."""
     cfg, wl, dM = _small_problem("d64", seed=8)
     w, X = wl.weights(), wl.patches()
     rng = np.random.default_rng(5)
@@ -372,8 +372,8 @@ def test_full_depth_gradients_one_item():
 # Reduced-depth Qwen2-VL-ViT shape at the sizes where the benchmark's weight-gradient
 # route runs: every weight-gradient GEMM has K (tokens) >= 2048, so the planner splits
 # K, the TN kernel writes fp32 partials and the split-K reduction adds them into
-# d_weights; M >= 512, so the fc1 bias sums come from the GELU-backward GEMM epilogue;
-# the side stream is on (the default), as in the benchmark.
+# d_weights; the GELU-backward GEMM has a large tile for each CU, so the fc1 bias sums come
+# from its epilogue; rows x hidden is past 2^20, so the side stream is on, as in the benchmark.
 # ---------------------------------------------------------------------------
 
 def _qwen_reduced(layers=1):

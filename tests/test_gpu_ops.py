@@ -27,8 +27,9 @@ def _ref_product(layout, A, B):
 
 
 GEMM_SHAPES = {
-    # small shapes use the 128x128 kernel; M >= 512 and N >= 256 use the 256x256 kernel
-    # (the large kernel's K pipeline: 1 to 3 tiles, ragged last tiles, several passes)
+    # bf16: 64x64 tiles, or the general kernel where N % 8 != 0 (test_gemm_large_kernels has
+    # the large ones); fp32: the 32x32 kernel.  K pipelines: 1 to 3 tiles, ragged last tiles,
+    # several passes
     NT: [(300, 200, 256), (1, 8, 8), (129, 257, 72), (512, 384, 1280), (700, 520, 200),
          (1030, 588, 64), (600, 300, 24), (520, 264, 96), (515, 260, 168), (520, 264, 264),
          (530, 256, 1000)],
@@ -66,10 +67,10 @@ def test_gemm_layouts(dtype, layout):
                                          ("bf16", 700, 392, 256), ("bf16", 530, 300, 64),
                                          ("bf16", 1100, 520, 360)])
 def test_gemm_epilogues(dtype, M, N, K, layout):
-    """Fused epilogues; (700, 392) and (1100, 520) run the large-tile kernels (256x256
-    tiles for NT, 128x256 for NN); (530, 300) has N % 8 != 0 (rows that break 16-byte
-    alignment), which the dispatcher sends to the general kernel.  NN takes the weight
-    as [K][N]."""
+    """Fused epilogues of 64x64 tiles (bf16) and of the 32x32 kernel (fp32); (530, 300) has
+    N % 8 != 0 (rows that break 16-byte alignment), which the dispatcher sends to the general
+    kernel.  NN takes the weight as [K][N].  (test_gemm_epilogues_by_kernel has the other
+    kernels.)"""
     import paper_2607_03229_amd as mp
     torch, dev = torch_dev()
     rng = np.random.default_rng(7)
@@ -385,11 +386,10 @@ def test_gemm_f32_tiles(layout):
 
 @pytest.mark.parametrize("layout", [NT, NN, TN])
 def test_gemm_bf16_small_tiles(layout):
-    """bf16 products of few tiles at the edges of the 64x64, 64x128 and 128x128 kernels: K of
-    less than one 64-deep tile, with an odd remainder, of a ring's depth more or less, and
-    sizes on which each tile is the one chosen (2,560 x 1,280 runs 128x128, 1,408 x 1,280
-    64x128).  Products that the large kernel also runs have its K order, so their rows are the
-    same bits as those of a taller product (1,400 rows alone and within 6,000)."""
+    """bf16 products of few tiles, nearly all on 64x64 ones: K of less than one 64-deep tile,
+    with an odd remainder, of a ring's depth more or less.  Rows are the same bits as those of
+    a taller product (200 and 1,400 rows alone and within 6,000, which run 128x128 tiles for NT
+    and the large ones for NN; test_gemm_bf16_rows_have_one_value has all four)."""
     import paper_2607_03229_amd as mp
     torch, dev = torch_dev()
     rng = np.random.default_rng(60 + layout)
@@ -545,3 +545,138 @@ def test_attention_f32_at_any_float(d):
     torch.cuda.synchronize()
     assert torch.isfinite(outs[0][2]).all()
     assert all(torch.equal(a, b) for out in outs[1:] for a, b in zip(outs[0], out))
+
+
+# ---- one kernel at a time: the sizes below name the kernel that runs them, and
+# ---- gemm_kernel has to agree ---------------------------------------------------------
+
+def _dev_max_rel(x, ref):
+    """max |x - ref| / max |ref| on the device, NaN if either side holds one"""
+    return float((x.double() - ref).abs().max() / ref.abs().max())
+
+
+def _gemm_operands(layout, dtype, M, N, K, seed):
+    """Device operands of a product (rows of a K-major B padded to 8) and, in float64, A and B
+    as [M][K] and [K][N]."""
+    torch, dev = torch_dev()
+    gen = torch.Generator(device=dev).manual_seed(seed)
+    t = torch.bfloat16 if dtype == "bf16" else torch.float32
+    ldb = K if layout == NT else (N + 7) // 8 * 8
+    A = torch.randn((K, M) if layout == TN else (M, K), device=dev, generator=gen).to(t)
+    B = torch.randn((N if layout == NT else K, ldb), device=dev, generator=gen).to(t)
+    A64, B64 = A.double(), B.double()
+    return A, B, ldb, A64.T if layout == TN else A64, B64.T if layout == NT else B64[:, :N]
+
+
+@pytest.mark.parametrize("layout,M,N,Ks", [
+    (NT, 4100, 4360, (8, 64, 72, 136, 200, 264, 328, 520, 1000)),
+    (NN, 5000, 2056, (8, 40, 64, 72, 136, 200, 264, 328, 520, 1000)),
+    (TN, 2056, 2312, (1, 5, 63, 64, 77, 128, 250, 291, 700))])
+def test_gemm_large_kernels(layout, M, N, Ks):
+    """The large bf16 kernels on ragged M, N and K: less than a K tile, one to three, ragged
+    last ones, several passes.  Against the product of the same values in float64; 1e-5 as for
+    the other fp32 outputs."""
+    import paper_2607_03229_amd as mp
+    torch_dev()   # (torch's HIP runtime is loaded before the library)
+    for K in Ks:
+        assert mp.gemm_kernel(1, layout, E_F32, M, N, K) == "large"
+        announce(f"gemm large kernel layout={layout} M={M} N={N} K={K}")
+        A, B, ldb, A64, B64 = _gemm_operands(layout, "bf16", M, N, K, K)
+        C = nans((M, N), "f32")
+        mp.op_gemm(1, layout, E_F32, M, N, K, A, A.shape[1], B, ldb, C, N)
+        assert _dev_max_rel(C, A64 @ B64) < 1e-5, K
+
+
+@pytest.mark.parametrize("kernel,dtype,layout,M,N,K", [
+    ("large", "bf16", NT, 4100, 4360, 200), ("large", "bf16", NN, 5000, 2056, 136),
+    ("large", "bf16", NN, 5000, 2056, 1000),
+    ("64x128", "bf16", NT, 645, 2040, 2040), ("64x128", "bf16", NN, 645, 2040, 2040),
+    ("128x128", "bf16", NT, 1100, 2040, 2040), ("128x128", "bf16", NN, 1100, 2040, 2040),
+    ("general", "bf16", NT, 1100, 1026, 200), ("general", "bf16", NN, 1100, 1026, 200),
+    ("general", "f32", NT, 1430, 1426, 100), ("general", "f32", NN, 1430, 1426, 100),
+    ("general", "f32", NN, 2050, 1283, 388)])
+def test_gemm_epilogues_by_kernel(kernel, dtype, layout, M, N, K):
+    """Every epilogue of each kernel that test_gemm_epilogues' sizes don't reach, with the
+    bounds of that test, against float64."""
+    import paper_2607_03229_amd as mp
+    torch, dev = torch_dev()
+    dt, tol = _dt(dtype), TOL[dtype]
+    A, B, ldb, A64, _ = _gemm_operands(layout, dtype, M, N, K, M)
+    t = A.dtype
+    B = (B.float() * 0.1).to(t)
+    B64 = B.double().T if layout == NT else B.double()[:, :N]
+    gen = torch.Generator(device=dev).manual_seed(1)
+    bias = torch.randn(N, device=dev, generator=gen).to(t)
+    acc = A64 @ B64
+    u = acc + bias.double()
+    phi = torch.special.ndtr(u)
+    dgelu = phi + u * torch.exp(-0.5 * u * u) / np.sqrt(2 * np.pi)
+
+    def go(epi, C, **kw):
+        assert mp.gemm_kernel(dt, layout, epi, M, N, K) == kernel
+        announce(f"{kernel} {dtype} layout={layout} M={M} N={N} K={K} epilogue {epi}")
+        mp.op_gemm(dt, layout, epi, M, N, K, A, A.shape[1], B, ldb, C, N, **kw)
+        return C
+
+    assert _dev_max_rel(go(E_STORE, nans((M, N), dtype), bias=bias), u) < tol
+    C2 = nans((M, N), dtype)
+    assert _dev_max_rel(go(E_GELU, nans((M, N), dtype), bias=bias, C2=C2, ldc2=N), u * phi) < tol
+    assert _dev_max_rel(C2, dgelu) < tol
+    assert _dev_max_rel(go(E_GELU, nans((M, N), dtype), bias=bias), u * phi) < tol
+    R = torch.randn((M, N), device=dev, generator=gen)
+    assert _dev_max_rel(go(E_RESID, R.clone(), bias=bias, aux=R, ld_aux=N), R.double() + u) < 2e-5
+    C = R.clone()   # in place
+    assert _dev_max_rel(go(E_RESID, C, bias=bias, aux=C, ld_aux=N), R.double() + u) < 2e-5
+    assert _dev_max_rel(go(E_RESID, nans((M, N), "f32"), bias=bias), u) < 2e-5
+    G = torch.rand((M, N), device=dev, generator=gen).to(t)
+    assert _dev_max_rel(go(E_GELUBWD, nans((M, N), dtype), aux=G, ld_aux=N),
+                        acc * G.double()) < tol
+    assert _dev_max_rel(go(E_F32, R.clone(), beta=1), R.double() + acc) < 2e-5
+
+
+@pytest.mark.parametrize("kernel,dtype,layout,M,N,K,kps", [
+    ("large", "bf16", NT, 4100, 4360, 200, 128), ("large", "bf16", NN, 5000, 2056, 200, 64),
+    ("large", "bf16", TN, 1040, 1032, 4100, 1088), ("general", "f32", TN, 700, 700, 1001, 256),
+    ("general", "f32", NN, 700, 700, 1000, 256), ("general", "f32", NT, 700, 700, 1000, 256),
+    ("f32_32x32", "f32", NN, 333, 264, 1000, 320)])
+def test_gemm_split_k_by_kernel(kernel, dtype, layout, M, N, K, kps):
+    """K splits, each against its own range of K in float64."""
+    import paper_2607_03229_amd as mp
+    torch_dev()
+    assert mp.gemm_kernel(_dt(dtype), layout, E_F32, M, N, K, kps) == kernel
+    announce(f"split k {kernel} {dtype} layout={layout} M={M} N={N} K={K} kps={kps}")
+    A, B, ldb, A64, B64 = _gemm_operands(layout, dtype, M, N, K, kps)
+    splits = -(-K // kps)
+    part = nans((splits, M, N), "f32")
+    mp.op_gemm(_dt(dtype), layout, E_F32, M, N, K, A, A.shape[1], B, ldb, part, N,
+               k_per_split=kps, split_stride=M * N)
+    for s in range(splits):
+        sl = slice(s * kps, min(K, (s + 1) * kps))
+        assert _dev_max_rel(part[s], A64[:, sl] @ B64[sl]) < 2e-5, s
+
+
+@pytest.mark.parametrize("layout", [NT, NN])
+def test_gemm_bf16_rows_have_one_value(layout):
+    """5,000 rows run the large kernel, 1,100 of them 128x128 tiles, 645 64x128 and 200 64x64
+    (with K of 32 tiles less 8): the same bits from all four, plain, with GELU and with the
+    residual, as an item's rows may not change with what shares its micro-batch."""
+    import paper_2607_03229_amd as mp
+    torch, dev = torch_dev()
+    N = K = 2040
+    A, B, ldb, _, _ = _gemm_operands(layout, "bf16", 5000, N, K, 3)
+    B = (B.float() * 0.1).to(B.dtype)
+    gen = torch.Generator(device=dev).manual_seed(2)
+    bias = torch.randn(N, device=dev, generator=gen).to(B.dtype)
+    R = torch.randn((5000, N), device=dev, generator=gen)
+    for epi in (E_STORE, E_GELU, E_RESID, E_F32):
+        out = []
+        for rows, kernel in ((5000, "large"), (1100, "128x128"), (645, "64x128"), (200, "64x64")):
+            assert mp.gemm_kernel(1, layout, epi, rows, N, K) == kernel
+            announce(f"{kernel} layout={layout} epilogue {epi}, {rows} rows")
+            C = nans((rows, N), "f32" if epi in (E_RESID, E_F32) else "bf16")
+            mp.op_gemm(1, layout, epi, rows, N, K, A, A.shape[1], B, ldb, C, N,
+                       bias=None if epi == E_F32 else bias,
+                       aux=R if epi == E_RESID else None, ld_aux=N)
+            out.append(C)
+        assert torch.isfinite(out[0]).all()
+        assert all(torch.equal(out[0][:c.shape[0]], c) for c in out[1:]), epi
