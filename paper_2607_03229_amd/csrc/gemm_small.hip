@@ -363,7 +363,9 @@ template <bool AK, bool BKM, int EPI>
 hipError_t by_tile(const GemmArgs& a, int tile, hipStream_t s) {
   switch (tile) {
     case TILE_64x64: return launch<AK, BKM, 1, 1, 4, EPI>(a, s);
-    case TILE_64x128: return launch<AK, BKM, 1, 2, 6, EPI>(a, s);
+    case TILE_64x128:   // (choose_tile never takes it for a weight gradient)
+      if constexpr (!AK) return launch<AK, BKM, 1, 2, 6, EPI>(a, s);
+      break;
     case TILE_128x128: return launch<AK, BKM, 2, 2, 4, EPI>(a, s);
   }
   return hipErrorInvalidValue;

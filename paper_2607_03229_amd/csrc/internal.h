@@ -67,7 +67,7 @@ hipError_t partials_reduce(float* part, float* out, int64_t rows, int n, hipStre
 hipError_t gemm_big(int layout, int epi, const GemmArgs& a, hipStream_t s);
 
 // bf16 problems of few large tiles: tile TILE_64x64, TILE_64x128 or TILE_128x128 (plan.h),
-// the alignment rules of gemm_big, on any M and N; TN with EPI_F32 only
+// the alignment rules of gemm_big, on any M and N; TN with EPI_F32 only, not on 64x128
 hipError_t gemm_small(int layout, int epi, int tile, const GemmArgs& a, hipStream_t s);
 // fp32 problems of few 128x128 tiles: 32x32 tiles, K split over a block's waves; same
 // contract as gemm()

@@ -122,8 +122,8 @@ const TileTime kTileTime[3][4] = {
      {1200, 10000, 0, 0, -3000}},                                                        // NT
     {{380, 1100, 190, 1000, 0}, {305, 4600, 0, 0, -2000}, {467, 5200, 0, 0, -2700},
      {1440, 9600, 630, 7100, -2000}},                                                    // NN
-    {{344, 3000, 134, 2400, 0}, {361, 4500, 0, 0, -1500}, {550, 7400, 0, 0, -3100},
-     {1050, 16000, 0, 0, -3100}},                                                        // TN
+    {{344, 3000, 134, 2400, 0}, {0, 0, 0, 0, 0} /* 361, 4500: never the fastest */,
+     {550, 7400, 0, 0, -3100}, {1050, 16000, 0, 0, -3100}},                              // TN
 };
 
 // The large kernels need M >= 512 and N >= 256; they keep every product that gives each CU a
@@ -145,6 +145,7 @@ int choose_tile(int layout, int64_t M, int64_t N, int64_t K, int64_t splits,
   for (int t = TILE_64x64; t <= TILE_BIG; ++t) {
     if (t == TILE_BIG && !big) break;
     const TileTime& T = kTileTime[layout][t];
+    if (T.step == 0) continue;
     const int64_t n = blocks(t) * splits, slots = T.step1 > 0 ? 512 : 256;
     const bool half = T.step1 > 0 && n % slots > 0 && n % slots <= 256;   // the last round
     const int64_t rounds = (n + slots - 1) / slots - half;
