@@ -830,7 +830,7 @@ def main():
             torch.cuda.synchronize()
             kern_alone = enc.profile_read(stream)
             enc.profile(False)
-            enc.set_side_stream(True)
+            enc.set_side_stream(None)
 
     # scatter bandwidth, timed on its own, after a few untimed calls (the step leaves the
     # caches full of its dirty lines, whose write-back would be charged to the first ones)

@@ -237,10 +237,11 @@ class Encoder:
         keys = ("fwd_flops", "fwd_bytes", "fwd_seconds", "bwd_flops", "bwd_bytes", "bwd_seconds")
         return dict(zip(keys, list(out)))
 
-    def set_side_stream(self, enable: bool):
-        """Backward weight-gradient work on the handle's internal stream or not (default: on
-        it where the micro-batch is large enough to gain)."""
-        _check(self.L.mpipe_encoder_set_side_stream(self._h, int(enable)))
+    def set_side_stream(self, enable: Optional[bool]):
+        """Backward weight-gradient work on the handle's internal stream or not; None (the
+        default): on it where the micro-batch is large enough to gain."""
+        _check(self.L.mpipe_encoder_set_side_stream(self._h,
+                                                    -1 if enable is None else int(enable)))
 
     # -- kernel timing --
     def profile(self, enable: bool):

@@ -773,7 +773,7 @@ void mpipe_encoder_destroy(mpipe_encoder* e) {
 
 mpipe_status mpipe_encoder_set_side_stream(mpipe_encoder* e, int32_t enable) {
   MP_RET(check_handle(e));
-  e->side_mode = enable != 0;
+  e->side_mode = enable < 0 ? -1 : enable != 0;
   return MPIPE_OK;
 }
 

@@ -262,3 +262,11 @@ def test_gemm_tile_is_near_the_fastest(L, product):
         mp.gemm_kernel(1, layout, 4 if layout == 2 else 0, M, N, K))]
     assert took <= 1.1 * min(us)
     assert len(us) < 4 or took <= 1.05 * us[3]
+
+
+def test_side_stream_switch_takes_none(L):
+    """On, off and the library's own choice (host state, no device work)."""
+    enc = B.Encoder(W.CONFIGS["c1_tiny_fp32"].cfg)
+    for enable in (True, False, None, True, None):
+        enc.set_side_stream(enable)
+    enc.close()

@@ -18,11 +18,12 @@ TOL = {"f32": 1e-4, "bf16": 2e-2}
 class GpuRun:
     """Runs mpipe_encoder_fwd / _bwd through the C-ABI on device copies of the inputs."""
 
-    def __init__(self, cfg, weights, patches, cu, grid):
+    def __init__(self, cfg, weights, patches, cu, grid, side=None):
         import paper_2607_03229_amd as mp
         self.torch, self.dev = torch_dev()
         self.cfg, self.cu, self.grid = cfg, np.asarray(cu), np.asarray(grid)
         self.enc = mp.Encoder(cfg)
+        self.enc.set_side_stream(side)
         self.w = to_dev(weights, cfg.dtype)
         self.X = to_dev(patches, cfg.dtype)
 
@@ -85,9 +86,9 @@ def _per_tensor_errors(cfg, got, ref):
     return errs
 
 
-def _check_full(wl_cfg, w, X, cu, grid, d_merged, tol, label, precision="f64"):
+def _check_full(wl_cfg, w, X, cu, grid, d_merged, tol, label, precision="f64", side=None):
     announce(f"encoder fwd+bwd {label} N={len(X)}")
-    g = GpuRun(wl_cfg, w, X, cu, grid)
+    g = GpuRun(wl_cfg, w, X, cu, grid, side)
     out = g.run(True, d_merged=d_merged, want_dx=True)
     announce(f"oracle ({precision}) {label}")
     rc, rM, rdw, rdx = oracle.encoder(wl_cfg, w, X, cu, grid, True, d_merged=d_merged,
@@ -448,7 +449,7 @@ def _merger_slice(cfg):
     return slice(lo, off)
 
 
-def _check_merger_only(cfg, w, X, cu, grid, dM, tol, label):
+def _check_merger_only(cfg, w, X, cu, grid, dM, tol, label, side=None):
     """The merger is the trainable source: its gradients match the oracle, every other
     entry of d_weights keeps its bits, the forward is the frozen one bit for bit, and no
     patch gradient can be asked for."""
@@ -457,7 +458,7 @@ def _check_merger_only(cfg, w, X, cu, grid, dM, tol, label):
     ms = _merger_slice(cfg)
     init = np.full(w.shape, 7.25, np.float32)
     init[ms] = 0.0
-    g = GpuRun(cfg, w, X, cu, grid)
+    g = GpuRun(cfg, w, X, cu, grid, side)
     out = g.run(MERGER_ONLY, d_merged=dM, dw_init=init)
     frozen = g.run(False)
     assert out["status"] == 0
@@ -578,3 +579,34 @@ def test_fp32_items_keep_their_bits():
     _, rM, _, rdx = oracle.encoder(cfg, w, X[:728], [0, 728], grid[:1], True, d_merged=dM[:182],
                                    want_d_patches=True)
     assert max_rel(merged[:182], rM) < TOL["f32"] and max_rel(dx[:728], rdx) < TOL["f32"]
+
+
+def _side_launches(g, **kw):
+    """Launches on the handle's own stream in one trained step."""
+    g.enc.profile(True)
+    g.run(True, **kw)
+    rec = g.enc.profile_read()
+    g.enc.profile(False)
+    return sum(n for name, (n, _, _) in rec.items() if name.endswith("@side"))
+
+
+def test_side_stream_choice_can_be_given_back():
+    """set_side_stream(None) returns to the choice by size: no for 656 rows x 128, yes for
+    2,208 x 512 (past 2^20)."""
+    cfg, wl, dM = _small_problem("d64", seed=8)
+    announce("side stream: on, off and by size, small")
+    g = GpuRun(cfg, wl.weights(), wl.patches(), wl.cu_seqlens, wl.grid_thw)
+    seen = []
+    for side in (None, True, None, False, None):
+        g.enc.set_side_stream(side)
+        seen.append(_side_launches(g, d_merged=dM) > 0)
+    assert seen == [False, True, False, False, False]
+    wide = W.EncoderConfig(hidden=512, layers=1, heads=8, mlp=512, llm_hidden=64)
+    W.custom_spec("wide_d64", wide)
+    wl = W.make_workload("wide_d64", 0, grid_thw=np.array([[1, 46, 48]]))
+    dM = np.random.default_rng(0).standard_normal((wl.n_merged, 64)).astype(np.float32)
+    announce("side stream: off and by size, past 2^20")
+    g = GpuRun(wide, wl.weights(), wl.patches(), wl.cu_seqlens, wl.grid_thw, side=False)
+    assert _side_launches(g, d_merged=dM) == 0
+    g.enc.set_side_stream(None)
+    assert _side_launches(g, d_merged=dM) > 0
