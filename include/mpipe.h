@@ -189,10 +189,10 @@ mpipe_status mpipe_encoder_bwd(mpipe_encoder* enc, const void* weights, const vo
  * gradient buffer is produced and joined back before mpipe_encoder_bwd returns;
  * the caller's stream waits for them only before it overwrites a buffer they
  * read.  enable == 0: everything runs on the caller's stream.  enable < 0 (the
- * default): the library chooses by the micro-batch's size (the stream is used where
- * rows x hidden reaches 2^20; below, its hand-offs cost more than they hide).  The
- * results are bitwise the same either way (same kernels, same operands, same order
- * per output).  Overlapping backward calls on one handle are not supported. */
+ * default): the library chooses by the weight gradients' work (rows x hidden^2, dtype
+ * and mode; below some size the hand-offs cost more than they hide).  The results are
+ * bitwise the same either way (same kernels, same operands, same order per output).
+ * Overlapping backward calls on one handle are not supported. */
 mpipe_status mpipe_encoder_set_side_stream(mpipe_encoder* enc, int32_t enable);
 
 /* Seam Gather, local half (Table 2, Replicated -> Sharded, forward):

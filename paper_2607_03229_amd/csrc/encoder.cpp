@@ -264,10 +264,17 @@ hipError_t ensure_side(mpipe_encoder* e) {
 
 // Whether the backward's weight-gradient work is worth a stream of its own.  Each hand-off
 // between the streams costs some microseconds of events and waits (22 in a two-layer step),
-// which the overlap must give back.  Measured on MI355X, us per trained two-layer step on /
-// off (rows x hidden): fp32 164x128 514 / 287, 1040x384 988 / 974, bf16 256x1024 802 / 774;
-// 1408x1280 1492 / 1587, 2048x1024 1368 / 1416, 10528x1024 3869 / 4027.
-bool side_pays(const Cfg& c, const Plan& P) { return P.N * c.hidden >= (int64_t)1 << 20; }
+// which the overlap must give back: it grows with the weight gradients' work, rows x hidden^2,
+// in time five times as much in fp32.  Measured on MI355X, us per trained two-layer step on /
+// off (rows x hidden): bf16 1024x1024 1038 / 976, 1152x1024 1149 / 1142, 2048x1024 1469 / 1530,
+// 512x1280 1064 / 1080, 832x1280 1222 / 1301, 2112x1280 1967 / 2079; fp32 1024x128 571 / 481,
+// 1600x384 1567 / 1582, 2304x384 2954 / 3074, 9216x384 24241 / 24647.  With only the merger
+// trained: 1024x1024 482 / 454, 3072x1024 867 / 866, 1408x1280 746 / 734, 2112x1280 905 / 910,
+// 4096x1280 1295 / 1326.
+bool side_pays(const Cfg& c, const Plan& P) {
+  const double work = (double)P.N * c.hidden * c.hidden * (c.dtype == 0 ? 5 : 1);
+  return work >= (P.mode == MODE_MERGER ? 3.2e9 : 1.2e9);
+}
 
 mpipe_status upload_meta(mpipe_encoder* e, const Plan& P, char* ws, hipStream_t s) {
   const size_t bytes = P.meta_bytes;

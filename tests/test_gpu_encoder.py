@@ -374,7 +374,7 @@ def test_full_depth_gradients_one_item():
 # route runs: every weight-gradient GEMM has K (tokens) >= 2048, so the planner splits
 # K, the TN kernel writes fp32 partials and the split-K reduction adds them into
 # d_weights; the GELU-backward GEMM has a large tile for each CU, so the fc1 bias sums come
-# from its epilogue; rows x hidden is past 2^20, so the side stream is on, as in the benchmark.
+# from its epilogue; there is work enough for the side stream, as in the benchmark.
 # ---------------------------------------------------------------------------
 
 def _qwen_reduced(layers=1):
@@ -581,18 +581,18 @@ def test_fp32_items_keep_their_bits():
     assert max_rel(merged[:182], rM) < TOL["f32"] and max_rel(dx[:728], rdx) < TOL["f32"]
 
 
-def _side_launches(g, **kw):
-    """Launches on the handle's own stream in one trained step."""
+def _side_launches(g, mode=1, **kw):
+    """Launches on the handle's own stream in one step."""
     g.enc.profile(True)
-    g.run(True, **kw)
+    g.run(mode, **kw)
     rec = g.enc.profile_read()
     g.enc.profile(False)
     return sum(n for name, (n, _, _) in rec.items() if name.endswith("@side"))
 
 
 def test_side_stream_choice_can_be_given_back():
-    """set_side_stream(None) returns to the choice by size: no for 656 rows x 128, yes for
-    2,208 x 512 (past 2^20)."""
+    """set_side_stream(None) returns to the choice by rows x hidden^2: no for 656 rows of 128,
+    yes for 2,208 of 1,024 (past 1.2e9)."""
     cfg, wl, dM = _small_problem("d64", seed=8)
     announce("side stream: on, off and by size, small")
     g = GpuRun(cfg, wl.weights(), wl.patches(), wl.cu_seqlens, wl.grid_thw)
@@ -601,12 +601,30 @@ def test_side_stream_choice_can_be_given_back():
         g.enc.set_side_stream(side)
         seen.append(_side_launches(g, d_merged=dM) > 0)
     assert seen == [False, True, False, False, False]
-    wide = W.EncoderConfig(hidden=512, layers=1, heads=8, mlp=512, llm_hidden=64)
+    wide = W.EncoderConfig(hidden=1024, layers=1, heads=16, mlp=512, llm_hidden=64)
     W.custom_spec("wide_d64", wide)
     wl = W.make_workload("wide_d64", 0, grid_thw=np.array([[1, 46, 48]]))
     dM = np.random.default_rng(0).standard_normal((wl.n_merged, 64)).astype(np.float32)
-    announce("side stream: off and by size, past 2^20")
+    announce("side stream: off and by size, large")
     g = GpuRun(wide, wl.weights(), wl.patches(), wl.cu_seqlens, wl.grid_thw, side=False)
     assert _side_launches(g, d_merged=dM) == 0
     g.enc.set_side_stream(None)
     assert _side_launches(g, d_merged=dM) > 0
+
+
+def test_side_stream_by_size_takes_the_fast_side():
+    """The library's choice at sizes where the two were measured 3 to 16 % apart: fp32 rows of
+    384 gain from the stream at 2,304 rows, rows of 128 lose at 1,024; bf16 rows of 1,280 gain
+    at 832, rows of 1,024 lose at 1,024, and with only the merger trained lose at 896."""
+    for hidden, heads, dtype, grid, mode, on in (
+            (384, 6, "f32", [1, 48, 48], 1, True), (128, 4, "f32", [1, 32, 32], 1, False),
+            (1280, 16, "bf16", [1, 26, 32], 1, True), (1024, 16, "bf16", [1, 32, 32], 1, False),
+            (1024, 16, "bf16", [1, 28, 32], 2, False)):
+        cfg = W.EncoderConfig(hidden=hidden, layers=1, heads=heads, mlp=512, llm_hidden=64,
+                              dtype=dtype)
+        W.custom_spec("side_size", cfg)
+        wl = W.make_workload("side_size", 0, grid_thw=np.array([grid]))
+        dM = np.random.default_rng(0).standard_normal((wl.n_merged, 64)).astype(np.float32)
+        announce(f"side stream by size: {dtype} {wl.n_patches} x {hidden} mode {mode}")
+        g = GpuRun(cfg, wl.weights(), wl.patches(), wl.cu_seqlens, wl.grid_thw)
+        assert (_side_launches(g, mode, d_merged=dM) > 0) == on
