@@ -628,3 +628,39 @@ def test_side_stream_by_size_takes_the_fast_side():
         announce(f"side stream by size: {dtype} {wl.n_patches} x {hidden} mode {mode}")
         g = GpuRun(cfg, wl.weights(), wl.patches(), wl.cu_seqlens, wl.grid_thw)
         assert (_side_launches(g, mode, d_merged=dM) > 0) == on
+
+
+@pytest.mark.parametrize("key", ["c1", "d64", "d80"])
+def test_small_problems_on_the_side_stream(key):
+    """Problems whose size alone keeps everything on the caller's stream, with the weight
+    gradients on the handle's: canaries, every gradient against the oracle, accumulation into
+    a d_weights that holds a value, and the merger-only mode."""
+    if key == "c1":
+        wl = W.make_workload("c1_tiny_fp32", 3)
+        cfg, dM = wl.cfg, wl.d_merged()
+    else:
+        cfg, wl, dM = _small_problem(key, seed=9)
+    w, X, cu, grid = wl.weights(), wl.patches(), wl.cu_seqlens, wl.grid_thw
+    one = _check_full(cfg, w, X, cu, grid, dM, TOL[cfg.dtype], f"{key} side stream", side=True)
+    base = np.random.default_rng(1).standard_normal(w.shape).astype(np.float32)
+    acc = GpuRun(cfg, w, X, cu, grid, side=True).run(True, d_merged=dM, dw_init=base)
+    np.testing.assert_array_equal(host(acc["dw"]).astype(np.float32),
+                                  base + host(one["dw"]).astype(np.float32))
+    _check_merger_only(cfg, w, X, cu, grid, dM, TOL[cfg.dtype], f"{key} side stream", side=True)
+
+
+def test_side_stream_with_fused_bias_sums():
+    """2,208 rows x 4,096 give the GELU-backward product a large tile for each CU, so it writes
+    the fc1 bias sums itself: the same bits on either stream, and against the oracle."""
+    import paper_2607_03229_amd as mp
+    torch_dev()
+    cfg = W.EncoderConfig(hidden=128, layers=2, heads=2, mlp=4096, llm_hidden=64)
+    W.custom_spec("fused_sums", cfg)
+    wl = W.make_workload("fused_sums", 0, grid_thw=np.array([[1, 46, 48]]))
+    assert mp.gemm_kernel(1, 1, 3, wl.n_patches, cfg.mlp, cfg.hidden) == "large"
+    w, X, cu, grid = wl.weights(), wl.patches(), wl.cu_seqlens, wl.grid_thw
+    dM = W.round_bf16(np.random.default_rng(6).standard_normal(
+        (wl.n_merged, cfg.llm_hidden)).astype(np.float32))
+    on = _check_full(cfg, w, X, cu, grid, dM, TOL["bf16"], "fused sums, side stream", side=True)
+    off = GpuRun(cfg, w, X, cu, grid, side=False).run(True, d_merged=dM, want_dx=True)
+    assert on["dw"].equal(off["dw"]) and on["dx"].equal(off["dx"])
