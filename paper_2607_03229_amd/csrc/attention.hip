@@ -1077,7 +1077,10 @@ __global__ __launch_bounds__(256) void attn_bwd_dkdv_f32_kernel(AttnArgs p) {
 // otherwise leave CUs idle while each wave walks its two sub-tiles; past that the second use
 // of a fragment is worth more.  Measured on MI355X, us a pass, whole items -> halves: 32 frozen
 // layers at 256 rows x 16 heads of 80 (32 pairs) 2873 -> 2812, two at 768 rows x 16 of 64 (96)
-// 265.5 -> 255.7, two trained at 1,408 rows x 16 of 80 (176) 1537 -> 1518.
+// 265.5 -> 255.7, two trained at 1,408 rows x 16 of 80 (176) 1537 -> 1518.  At the line, us of
+// forward / dQ / dK/dV with their event brackets, one segment, d = 64: 256 pairs 45.7 / 47.1 /
+// 64.0 -> 39.3 / 45.6 / 65.7; 288 pairs 55.9 / 65.9 / 87.1 -> 51.9 / 63.5 / 114.2 (two dK/dV
+// blocks fit a CU: past 512 half items a second round starts); d = 80 and eight segments alike.
 constexpr int64_t SMALL_PAIRS = 256;
 bool small_pairs(const AttnArgs& a) { return (int64_t)a.n_work * a.heads <= SMALL_PAIRS; }
 

@@ -350,7 +350,9 @@ __global__ __launch_bounds__(64) void reduce_partials_stage2(PartialSet ps, int6
 // rows w, w + 16, ..., eight loads in flight, the sixteen wave sums added in order).  Up to
 // RED_SINGLE rows this is one short latency chain instead of two launches with a dependence
 // between them: us, two stages -> one, 352 rows x 3 sets of 1,280 columns 5.5 + 9.9 -> 6.2,
-// 41 rows x 3 of 128 2.6 + 2.9 -> 3.2, 22 rows of 5,120 5.2 + 4.2 -> 4.6.
+// 41 rows x 3 of 128 2.6 + 2.9 -> 3.2, 22 rows of 5,120 5.2 + 4.2 -> 4.6.  (Three sets of
+// 1,280, with the event brackets: 512 rows 11.4 -> 7.0, 768 11.3 -> 8.4, 1,024 11.3 -> 8.4:
+// the line could lie higher, at the price of another order of those sums.)
 constexpr int64_t RED_SINGLE = 512;
 __global__ __launch_bounds__(1024) void reduce_partials_single(PartialSet ps, int64_t nb, int n) {
   __shared__ float red[16][64];

@@ -164,7 +164,9 @@ GemmSplit choose_split(int64_t M, int64_t N, int64_t K) {
   // Weight-gradient GEMMs have few output tiles and a long K (tokens): split K so
   // the grid fills whole rounds of 256 CUs as far as the cap allows (each split keeps
   // >= 1024 rows of K).
-  // Tile size follows the kernel the GEMM dispatches to (256 when M >= 512, N >= 256).
+  // Tiles are counted as the large kernel's (one block per CU) where it can take the product,
+  // else as 128x128 ones at two per CU.  choose_tile may give a product another tile; the
+  // split does not follow it.
   const bool big = M >= 512 && N >= 256;
   const int64_t t = big ? 256 : 128;
   const int64_t tiles = ((M + t - 1) / t) * ((N + t - 1) / t);
