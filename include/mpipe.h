@@ -137,7 +137,10 @@ mpipe_status mpipe_param_info(const mpipe_encoder_cfg* cfg, int32_t i, char* nam
 
 /* Buffer sizes for one micro-batch in a trainability mode (mpipe_train_mode):
  * device workspace, tape (0 when frozen, the merger's inputs only for
- * MPIPE_TRAIN_MERGER), merged rows and packed patch rows.  Validates the metadata. */
+ * MPIPE_TRAIN_MERGER), merged rows and packed patch rows.  Validates the metadata.
+ * The workspace holds room for a padded copy of the patch rows and their weight
+ * whatever their alignment, which this call does not know; the copy is made only
+ * where rows or pointers are off 16 bytes. */
 mpipe_status mpipe_encoder_sizes(const mpipe_encoder* enc, const int32_t* cu_seqlens,
                                  int32_t n_seg, const int32_t* grid_thw, int32_t n_items,
                                  int32_t trainable, size_t* workspace_bytes, size_t* tape_bytes,

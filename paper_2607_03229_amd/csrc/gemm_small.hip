@@ -14,11 +14,13 @@
 // t + 2 .. t + NST are in flight; one barrier per tile.  What bounds it is LDS bandwidth (a
 // 64x64 tile reads each fragment for one MFMA: 32 KB of reads and 16 KB of DMA writes per
 // K tile, about 400 cycles of which 128 are MFMA), which the larger tiles halve; rings deeper
-// than these did not help (64x64, 8 stages: 20.3 us against 18.7 at 256x1280x5120).
-// Measured on MI355X, us, the former kernel on a transposed weight -> this one, NT:
-// 256x1280x1280 27 -> 8.7, 256x5120x1280 27 -> 10.3, 256x1280x5120 89 -> 18.5 (64x64);
-// 1408x1280x5120 56 -> 30 (64x128); 2700x1280x5120 57 -> 43 (128x128).  TN
-// 1280x1280x1408 34 -> 13.
+// than these did not help back to back (64x64, 8 stages: 20.3 us against 18.7 at
+// 256x1280x5120).
+// Measured on MI355X, us back to back, the former kernel on a transposed weight -> this one,
+// NT: 256x1280x1280 27 -> 8.7, 256x5120x1280 27 -> 10.3, 256x1280x5120 89 -> 18.5 (64x64);
+// 648x2048x2048 15.3 (64x128, 64x64 14.1); 2700x1280x5120 57 -> 43 (128x128).  TN
+// 1280x1280x1408 34 -> 13.  In a 32-layer pass, whose weights and activations are not in
+// cache, the first three take 10, 16 and 27.
 #include <algorithm>
 #include <type_traits>
 
