@@ -845,9 +845,9 @@ __global__ __launch_bounds__(256) void attn_fwd_f32_kernel(AttnArgs p) {
   __shared__ f32x4 red[3 * ND][64];
   __shared__ float2 ml[4][64];
   const int sub = blockIdx.x % F32_SUB;
-  const uint32_t pair = p.pair0 + blockIdx.x / F32_SUB;
-  const int4 wk = p.work[pair / (uint32_t)p.heads];
-  const int head = (int)(pair % (uint32_t)p.heads);
+  const int wh = blockIdx.x / F32_SUB;
+  const int4 wk = p.work[wh / p.heads];
+  const int head = wh % p.heads;
   const int q0 = wk.x + 16 * sub, s0 = wk.y, last = wk.z - 1;
   if (q0 > last) return;
   const int w = threadIdx.x >> 6, l = threadIdx.x & 63, g = l >> 4, r = l & 15;
@@ -925,9 +925,9 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_f32_kernel(AttnArgs p) {
   constexpr int ND = D / 16;
   __shared__ f32x4 red[3 * ND][64];
   const int sub = blockIdx.x % F32_SUB;
-  const uint32_t pair = p.pair0 + blockIdx.x / F32_SUB;
-  const int4 wk = p.work[pair / (uint32_t)p.heads];
-  const int head = (int)(pair % (uint32_t)p.heads);
+  const int wh = blockIdx.x / F32_SUB;
+  const int4 wk = p.work[wh / p.heads];
+  const int head = wh % p.heads;
   const int q0 = wk.x + 16 * sub, s0 = wk.y, last = wk.z - 1;
   if (q0 > last) return;
   const int w = threadIdx.x >> 6, l = threadIdx.x & 63, g = l >> 4, r = l & 15;
@@ -995,9 +995,9 @@ __global__ __launch_bounds__(256) void attn_bwd_dkdv_f32_kernel(AttnArgs p) {
   constexpr int ND = D / 16;
   __shared__ f32x4 red[3 * ND][64];
   const int sub = blockIdx.x % F32_SUB;
-  const uint32_t pair = p.pair0 + blockIdx.x / F32_SUB;
-  const int4 wk = p.work[pair / (uint32_t)p.heads];
-  const int head = (int)(pair % (uint32_t)p.heads);
+  const int wh = blockIdx.x / F32_SUB;
+  const int4 wk = p.work[wh / p.heads];
+  const int head = wh % p.heads;
   const int key0 = wk.x + 16 * sub, s0 = wk.y, last = wk.z - 1;
   if (key0 > last) return;
   const int w = threadIdx.x >> 6, l = threadIdx.x & 63, g = l >> 4, r = l & 15;
@@ -1084,59 +1084,54 @@ __global__ __launch_bounds__(256) void attn_bwd_dkdv_f32_kernel(AttnArgs p) {
 constexpr int64_t SMALL_PAIRS = 256;
 bool small_pairs(const AttnArgs& a) { return (int64_t)a.n_work * a.heads <= SMALL_PAIRS; }
 
-template <int D>
-hipError_t fwd_bf16(const AttnArgs& a, hipStream_t s) {
-  if (small_pairs(a))
-    hipLaunchKernelGGL((attn_fwd_kernel<D, 1>), dim3(2 * a.n_work * a.heads), dim3(64 * NW), 0, s, a);
-  else
-    hipLaunchKernelGGL((attn_fwd_kernel<D, 2>), dim3(a.n_work * a.heads), dim3(64 * NW), 0, s, a);
-  return hipGetLastError();
-}
-template <int D>
-hipError_t dq_bf16(const AttnArgs& a, hipStream_t s) {
-  if (small_pairs(a))
-    hipLaunchKernelGGL((attn_bwd_dq_kernel<D, 1>), dim3(2 * a.n_work * a.heads), dim3(64 * NW), 0, s, a);
-  else
-    hipLaunchKernelGGL((attn_bwd_dq_kernel<D, 2>), dim3(a.n_work * a.heads), dim3(64 * NW), 0, s, a);
-  return hipGetLastError();
-}
-template <int D>
-hipError_t dkdv_bf16(const AttnArgs& a, hipStream_t s) {
-  if (small_pairs(a))
-    hipLaunchKernelGGL((attn_bwd_dkdv_kernel<D, 1>), dim3(2 * a.n_work * a.heads), dim3(64 * NW), 0, s, a);
-  else
-    hipLaunchKernelGGL((attn_bwd_dkdv_kernel<D, 2>), dim3(a.n_work * a.heads), dim3(64 * NW), 0, s, a);
-  return hipGetLastError();
-}
-// fp32: eight blocks of 256 threads per (work item, head) pair, launched 2^20 pairs at a time,
-// since one launch is limited to 2^32 threads (one-row segments reach that at 131,073 rows of
-// 16 heads).
-constexpr int64_t F32_PAIRS = 1 << 20;
+// `per_pair` blocks of 256 threads for each (work item, head) pair.  A launch holds fewer than
+// 2^32 threads, and the runtime starts part of a larger one without an error, so the work list
+// is launched in pieces of at most 2^23 blocks (one-row segments of 16 heads: from 65,537 rows
+// in fp32, eight blocks a pair, and 524,289 in bf16).
+constexpr int64_t MAX_BLOCKS = 1 << 23;
 template <class Kernel>
-hipError_t launch_f32(Kernel kernel, const AttnArgs& a0, hipStream_t s) {
+hipError_t launch(Kernel kernel, const AttnArgs& a0, int per_pair, hipStream_t s) {
+  const int64_t per_item = (int64_t)per_pair * a0.heads;
+  if (per_item > MAX_BLOCKS) return hipErrorInvalidConfiguration;
+  const int64_t step = MAX_BLOCKS / per_item;
   AttnArgs a = a0;
-  const int64_t pairs = (int64_t)a.n_work * a.heads;
-  if (pairs > INT32_MAX) return hipErrorInvalidConfiguration;
-  for (int64_t p0 = 0; p0 < pairs; p0 += F32_PAIRS) {
-    a.pair0 = (uint32_t)p0;
-    const int64_t n = pairs - p0 < F32_PAIRS ? pairs - p0 : F32_PAIRS;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)(n * F32_SUB)), dim3(256), 0, s, a);
+  for (int64_t w = 0; w < a0.n_work; w += step) {
+    a.work = a0.work + w;
+    a.n_work = (int)(a0.n_work - w < step ? a0.n_work - w : step);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(a.n_work * per_item)), dim3(256), 0, s, a);
     const hipError_t r = hipGetLastError();
     if (r != hipSuccess) return r;
   }
   return hipSuccess;
 }
+static_assert(64 * NW == 256, "attention blocks are 256 threads");
+
+template <int D>
+hipError_t fwd_bf16(const AttnArgs& a, hipStream_t s) {
+  return small_pairs(a) ? launch(attn_fwd_kernel<D, 1>, a, 2, s)
+                        : launch(attn_fwd_kernel<D, 2>, a, 1, s);
+}
+template <int D>
+hipError_t dq_bf16(const AttnArgs& a, hipStream_t s) {
+  return small_pairs(a) ? launch(attn_bwd_dq_kernel<D, 1>, a, 2, s)
+                        : launch(attn_bwd_dq_kernel<D, 2>, a, 1, s);
+}
+template <int D>
+hipError_t dkdv_bf16(const AttnArgs& a, hipStream_t s) {
+  return small_pairs(a) ? launch(attn_bwd_dkdv_kernel<D, 1>, a, 2, s)
+                        : launch(attn_bwd_dkdv_kernel<D, 2>, a, 1, s);
+}
 template <int D>
 hipError_t fwd_f32(const AttnArgs& a, hipStream_t s) {
-  return launch_f32(attn_fwd_f32_kernel<D>, a, s);
+  return launch(attn_fwd_f32_kernel<D>, a, F32_SUB, s);
 }
 template <int D>
 hipError_t dq_f32(const AttnArgs& a, hipStream_t s) {
-  return launch_f32(attn_bwd_dq_f32_kernel<D>, a, s);
+  return launch(attn_bwd_dq_f32_kernel<D>, a, F32_SUB, s);
 }
 template <int D>
 hipError_t dkdv_f32(const AttnArgs& a, hipStream_t s) {
-  return launch_f32(attn_bwd_dkdv_f32_kernel<D>, a, s);
+  return launch(attn_bwd_dkdv_f32_kernel<D>, a, F32_SUB, s);
 }
 
 }  // namespace

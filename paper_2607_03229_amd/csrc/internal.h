@@ -93,7 +93,6 @@ struct AttnArgs {
   float* delta_out = nullptr;
   const int4* work = nullptr;  // (tile start row, segment start, segment end, 0)
   int n_work = 0;
-  uint32_t pair0 = 0;   // fp32 kernels: first (work item, head) pair of this launch
   int heads = 0;
   int64_t N = 0;
   float scale = 0.f;

@@ -495,27 +495,30 @@ def test_gemm_f32_rows_of_a_taller_product(layout, N, K):
         assert all(torch.equal(out[0][:c.shape[0]], c) for c in out[1:]), epi
 
 
-def test_attention_f32_more_pairs_than_one_launch():
-    """131,200 one-row segments of 16 heads are 2,099,200 (segment, head) pairs, more than
-    eight blocks of 256 threads each fit into one launch (2^32 threads).  A row alone attends
-    to itself: O is V to the bit, dV is dO, and dQ, dK are the rounding of a zero (dP - delta,
-    32 terms of up to 30 in two orders, times |k| <= 6: below 1e-4)."""
+@pytest.mark.parametrize("dtype,N", [("f32", 131200), ("bf16", 1048640)])
+def test_attention_more_blocks_than_one_launch(dtype, N):
+    """One-row segments of 16 heads, more (segment, head) pairs than blocks of 256 threads fit
+    into one launch of 2^32 threads: 2,099,200 pairs of eight blocks (fp32), 16,778,240 of one
+    (bf16).  A row alone attends to itself: O is V to the bit, dV is dO to the type's rounding
+    (2^-8 of up to 6, and of the weight's own), and dQ, dK are the rounding of a zero
+    (dP - delta, 32 terms of up to 30 in two orders, times |k| <= 6: below 1e-4)."""
     import paper_2607_03229_amd as mp
     torch, dev = torch_dev()
-    N, heads, d = 131200, 16, 32
+    heads, d = 16, 32
     h = heads * d
-    announce(f"fp32 attention over {N} one-row segments, {heads} heads")
+    announce(f"{dtype} attention over {N} one-row segments, {heads} heads")
     gen = torch.Generator(device=dev).manual_seed(1)
-    qkv = torch.randn((N, 3 * h), device=dev, generator=gen)
-    dO = torch.randn((N, h), device=dev, generator=gen)
-    o, lse, dqkv = nans((N, h), "f32"), nans((heads, N), "f32"), nans((N, 3 * h), "f32")
+    t = torch.bfloat16 if dtype == "bf16" else torch.float32
+    qkv = torch.randn((N, 3 * h), device=dev, generator=gen, dtype=t)
+    dO = torch.randn((N, h), device=dev, generator=gen, dtype=t)
+    o, lse, dqkv = nans((N, h), dtype), nans((heads, N), "f32"), nans((N, 3 * h), dtype)
     scratch = torch.empty(mp.op_scratch_bytes(N, heads, h, N), dtype=torch.uint8, device=dev)
     cu = np.arange(N + 1, dtype=np.int32)
-    mp.op_attention_fwd(0, qkv, N, heads, d, cu, o, lse, scratch)
-    mp.op_attention_bwd(0, qkv, o, dO, lse, N, heads, d, cu, dqkv, scratch)
+    mp.op_attention_fwd(_dt(dtype), qkv, N, heads, d, cu, o, lse, scratch)
+    mp.op_attention_bwd(_dt(dtype), qkv, o, dO, lse, N, heads, d, cu, dqkv, scratch)
     torch.cuda.synchronize()
     assert torch.equal(o, qkv[:, 2 * h:])
-    assert (dqkv[:, 2 * h:] - dO).abs().max() < 1e-4
+    assert (dqkv[:, 2 * h:] - dO).abs().max() < (6e-2 if dtype == "bf16" else 1e-4)
     assert dqkv[:, :2 * h].abs().max() < 1e-4
 
 
