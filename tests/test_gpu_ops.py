@@ -533,12 +533,13 @@ def test_attention_f32_at_any_float(d):
     cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
     announce(f"fp32 attention d={d} on tensors one to three floats off 16 bytes")
     gen = torch.Generator(device=dev).manual_seed(d)
-    qkv, dO = (torch.randn((N, n), device=dev, generator=gen) for n in (3 * h, h))
+    f32 = dict(dtype=torch.float32, device=dev)
+    qkv, dO = (torch.randn((N, n), generator=gen, **f32) for n in (3 * h, h))
     scratch = torch.empty(mp.op_scratch_bytes(N, heads, h, 3), dtype=torch.uint8, device=dev)
     outs = []
     for off in range(4):
         def at(t):
-            out = torch.full((t.numel() + 4,), float("nan"), device=dev)[off:off + t.numel()]
+            out = torch.full((t.numel() + 4,), float("nan"), **f32)[off:off + t.numel()]
             return out.view(t.shape).copy_(t)
         tq, tdo, o, dqkv = at(qkv), at(dO), at(torch.empty_like(dO)), at(torch.empty_like(qkv))
         lse = nans((heads, N), "f32")
@@ -626,7 +627,7 @@ def test_gemm_epilogues_by_kernel(kernel, dtype, layout, M, N, K):
     assert _dev_max_rel(go(E_GELU, nans((M, N), dtype), bias=bias, C2=C2, ldc2=N), u * phi) < tol
     assert _dev_max_rel(C2, dgelu) < tol
     assert _dev_max_rel(go(E_GELU, nans((M, N), dtype), bias=bias), u * phi) < tol
-    R = torch.randn((M, N), device=dev, generator=gen)
+    R = torch.randn((M, N), device=dev, generator=gen, dtype=torch.float32)
     assert _dev_max_rel(go(E_RESID, R.clone(), bias=bias, aux=R, ld_aux=N), R.double() + u) < 2e-5
     C = R.clone()   # in place
     assert _dev_max_rel(go(E_RESID, C, bias=bias, aux=C, ld_aux=N), R.double() + u) < 2e-5
@@ -670,7 +671,7 @@ def test_gemm_bf16_rows_have_one_value(layout):
     B = (B.float() * 0.1).to(B.dtype)
     gen = torch.Generator(device=dev).manual_seed(2)
     bias = torch.randn(N, device=dev, generator=gen).to(B.dtype)
-    R = torch.randn((5000, N), device=dev, generator=gen)
+    R = torch.randn((5000, N), device=dev, generator=gen, dtype=torch.float32)
     for epi in (E_STORE, E_GELU, E_RESID, E_F32):
         out = []
         for rows, kernel in ((5000, "large"), (1100, "128x128"), (645, "64x128"), (200, "64x64")):
